@@ -1,6 +1,8 @@
 // Dispatch of the per-class launchers (k<bits>.hip) by size-class index.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "pmk_internal.hpp"
 
 namespace pmk {
@@ -76,6 +78,49 @@ uint32_t exp_units(int cls, int decrypt, uint32_t ntiles) {
     // one wavefront per 64 / L chunks: encryption per tile, CRT halves per tile and prime
     const int bits = kClassBits[cls];
     return decrypt ? 2 * ntiles * (uint32_t)lanes_half(bits) : ntiles * (uint32_t)lanes_full(bits);
+}
+
+#define PMK_GROUP(B)                                     \
+    int launch_halves_group_##B(const ClassRun &, uint32_t, hipStream_t); \
+    uint32_t group_resident_##B();
+PMK_GROUP(1024)
+PMK_GROUP(2048)
+PMK_GROUP(3072)
+PMK_GROUP(4096)
+PMK_GROUP(6144)
+PMK_GROUP(8192)
+
+#define PMK_DISPATCH_GROUP(cls, FN, none, ...)     \
+    switch (kClassBits[cls]) {                     \
+        case 1024: return FN##_1024(__VA_ARGS__);  \
+        case 2048: return FN##_2048(__VA_ARGS__);  \
+        case 3072: return FN##_3072(__VA_ARGS__);  \
+        case 4096: return FN##_4096(__VA_ARGS__);  \
+        case 6144: return FN##_6144(__VA_ARGS__);  \
+        case 8192: return FN##_8192(__VA_ARGS__);  \
+        default: return none;                      \
+    }
+
+uint64_t group_slot_words(int cls, int win) {
+    return (uint64_t)(1u << (win - 1)) * fold_group(kClassBits[cls]).nl * 16;
+}
+uint32_t group_resident(int cls) { PMK_DISPATCH_GROUP(cls, group_resident, 0u) }
+int launch_halves_group(const ClassRun &r, uint32_t first, void *stream) {
+    PMK_DISPATCH_GROUP(r.cls, launch_halves_group, (int)hipErrorInvalidValue, r, first, (hipStream_t)stream)
+}
+
+uint64_t table_words(int cls, uint32_t slots_enc, uint32_t slots_dec, uint32_t ntiles, int win) {
+    uint64_t need = slots_enc * table_words_per_slot(cls, 0, 0);
+    need = std::max(need, slots_dec * table_words_per_slot(cls, 1, win));
+    if (fold_group(kClassBits[cls]).nl)
+        need = std::max(need, std::min<uint64_t>(8ull * ntiles, group_resident(cls)) * group_slot_words(cls, win));
+    return need;
+}
+
+uint32_t table_units(int cls, uint32_t ntiles) {
+    // fold form: a block's waves even where a group has fewer tiles
+    const int bits = kClassBits[cls];
+    return (fold_lane(bits).nl ? fold_lane_block(bits) : 1) * exp_units(cls, 1, ntiles);
 }
 
 uint32_t wave_slots(int cls, int decrypt, int num_cus) {

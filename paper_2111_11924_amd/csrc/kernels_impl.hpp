@@ -20,6 +20,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "fold.hpp"
 #include "mont.hpp"
 #include "mont_lanes.hpp"
 #include "pmk_internal.hpp"
@@ -473,14 +474,6 @@ PMK_DEV WinStep win_first(ExpWords &nx, const uint32_t *d, int SH, int top, int 
     return first;
 }
 
-// Sliding windows (odd-power table, 2^(w-1) entries) where they measured
-// faster: the one-lane classes up to 2048 bits (three waves per SIMD) and the
-// lane-group classes; the 3072/4096-bit one-lane halves (two waves per SIMD)
-// measured 6 % slower and 0 % faster with them and keep fixed windows (2^w
-// entries, T[0] = R mod p).
-template <int CB>
-constexpr bool kSlidingHalves = lanes_half(CB) > 1 || make_geom(CB).nlh <= 40;
-
 template <int CB>
 PMK_DEV void halves_unit(const ClassRun r, uint32_t jt, uint32_t *tbl, uint32_t *lds) {
     constexpr Geom G = make_geom(CB);
@@ -538,173 +531,99 @@ PMK_DEV void halves_unit(const ClassRun r, uint32_t jt, uint32_t *tbl, uint32_t 
     }
     load_limbs(b, hr + G.h_rr);
 
-    if constexpr (kSlidingHalves<CB>) {
-        const int TH = 1 << (win - 1);  // odd powers x~, x~^3, ..., x~^(2 TH - 1)
-        // One call site each for the product and the square keeps the loop's
-        // code within the instruction cache.  Phases:
-        //   0  MM(c_lo, R^2) = c_lo R mod p            (parked in entry 1)
-        //   1  MM(c_hi, R^3) = c_hi R^2 mod p; x~ = sum (below 4p) -> entry 0
-        //   2  x~^2 (the step between odd powers)
-        //   5  entry e = x~^(2e+1) = entry e-1 times x~^2, e = 1 .. TH-1
-        //   3  per window step: its squarings (while the step's odd power is
-        //      copied into LDS), then times that power
-        //   4  MM(., 1): leave Montgomery form
-        int phase = 0, e = 1, sq = 0;
-        WinStep st = WinStep::make(0, 0u, false, -1);
-        ExpWords nx{0u, 0u, 0u};
-        for (;;) {
-            if (phase == 3) {
-                if (sq < st.nsq()) {
-                    if (sq == 0 && st.mul()) prefetch_row4<NL>(lds, tbl, st.idx(), lane);
-                    mont_sqr<NL, LB>(acc, acc, n, n0);
-                    ++sq;
-                    continue;
-                }
-                if (st.mul()) {
-                    take_row4(b, lds, lane);
-                } else {  // trailing zero bits done
-#pragma unroll
-                    for (int j = 0; j < NL; ++j) b[j] = j == 0 ? 1u : 0u;
-                    phase = 4;
-                }
-            }
-            mont_mul<NL, LB>(acc, acc, b, n, n0);
-            if (phase == 4) break;
-            if (phase == 0) {
-                store_row4(tbl, 1, lane, acc);
-                load_row4(acc, tbl, 0, lane);
-                load_limbs(b, hr + G.h_rrr);
-                phase = 1;
-                // table-building steps leave nothing in flight: the wait the
-                // compiler puts where the window loop joins them would otherwise
-                // also wait for the window's prefetch
-                __builtin_amdgcn_s_waitcnt(0);
+    const int TH = 1 << (win - 1);  // odd powers x~, x~^3, ..., x~^(2 TH - 1)
+    // One call site each for the product and the square keeps the loop's
+    // code within the instruction cache.  Phases:
+    //   0  MM(c_lo, R^2) = c_lo R mod p            (parked in entry 1)
+    //   1  MM(c_hi, R^3) = c_hi R^2 mod p; x~ = sum (below 4p) -> entry 0
+    //   2  x~^2 (the step between odd powers)
+    //   5  entry e = x~^(2e+1) = entry e-1 times x~^2, e = 1 .. TH-1
+    //   3  per window step: its squarings (while the step's odd power is
+    //      copied into LDS), then times that power
+    //   4  MM(., 1): leave Montgomery form
+    int phase = 0, e = 1, sq = 0;
+    WinStep st = WinStep::make(0, 0u, false, -1);
+    ExpWords nx{0u, 0u, 0u};
+    for (;;) {
+        if (phase == 3) {
+            if (sq < st.nsq()) {
+                if (sq == 0 && st.mul()) prefetch_row4<NL>(lds, tbl, st.idx(), lane);
+                mont_sqr<NL, LB>(acc, acc, n, n0);
+                ++sq;
                 continue;
             }
-            if (phase == 1) {
-                load_row4(b, tbl, 1, lane);
-                uint32_t c = 0;
-#pragma unroll
-                for (int j = 0; j < NL; ++j) {
-                    const uint32_t v = acc[j] + b[j] + c;
-                    acc[j] = v & Radix<LB>::MASK;
-                    c = v >> LB;
-                }
-                store_row4(tbl, 0, lane, acc);
-#pragma unroll
-                for (int j = 0; j < NL; ++j) b[j] = acc[j];  // next: x~ x~
-                phase = 2;
-                __builtin_amdgcn_s_waitcnt(0);
-                continue;
-            }
-            if (phase == 2) {
-#pragma unroll
-                for (int j = 0; j < NL; ++j) b[j] = acc[j];  // x~^2, the multiplier of phase 5
-                load_row4(acc, tbl, 0, lane);
-                phase = 5;
-                __builtin_amdgcn_s_waitcnt(0);
-                continue;
-            }
-            if (phase == 5) {
-                store_row4(tbl, e, lane, acc);
-                ++e;
-                __builtin_amdgcn_s_waitcnt(0);
-                if (e < TH) continue;
-                // table complete: the first window starts at the top set bit
-                // (no squarings of 1); d = 0 gives the Montgomery one
-                const int top = exp_top_bit(dexp, SH);
-                if (top < 0) {
-                    load_limbs(acc, one_h);
-                    st = WinStep::make(0, 0u, false, -1);
-                } else {
-                    st = win_first(nx, dexp, SH, top, win);
-                    load_row4(acc, tbl, st.idx(), lane);
-                    win_advance(st, nx, dexp, SH, win);
-                }
-                __builtin_amdgcn_s_waitcnt(0);
-                phase = 3;
-                sq = 0;
-                continue;
-            }
-            // phase 3: the step's product is done
-            win_advance(st, nx, dexp, SH, win);
-            sq = 0;
-        }
-    } else {
-        // fixed windows of win bits from the top: T[k] = x~^k (T[0] = R mod p)
-        const int T = 1 << win;
-        const int NW = (32 * SH + win - 1) / win;  // digits of the exponent
-        // One call site each for the product and the square keeps the loop's
-        // code within the instruction cache.  Phases:
-        //   0  MM(c_lo, R^2) = c_lo R mod p            (parked in T[1])
-        //   1  MM(c_hi, R^3) = c_hi R^2 mod p; x~ = sum (below 4p), T[1] = x~
-        //   2  T[e] = T[e-1] x~ for e = 2 .. T-1
-        //   3  per digit below the top one: win squarings (while T[digit] is
-        //      copied into LDS), then times T[digit]
-        //   4  MM(., 1): leave Montgomery form
-        int phase = 0, e = 2, digit = NW - 2, sq = 0;
-        for (;;) {
-            if (phase == 3) {
-                if (sq < win) {
-                    if (sq == 0) prefetch_row4<NL>(lds, tbl, digit_of(dexp, SH, digit, win), lane);
-                    mont_sqr<NL, LB>(acc, acc, n, n0);
-                    ++sq;
-                    continue;
-                }
+            if (st.mul()) {
                 take_row4(b, lds, lane);
-            }
-            mont_mul<NL, LB>(acc, acc, b, n, n0);
-            if (phase == 4) break;
-            if (phase == 0) {
-                store_row4(tbl, 1, lane, acc);
-                load_row4(acc, tbl, 0, lane);
-                load_limbs(b, hr + G.h_rrr);
-                phase = 1;
-                // table-building steps leave nothing in flight: the wait the
-                // compiler puts where the digit loop joins them would otherwise
-                // also wait for the digit prefetch
-                __builtin_amdgcn_s_waitcnt(0);
-                continue;
-            }
-            if (phase == 1) {
-                load_row4(b, tbl, 1, lane);
-                uint32_t c = 0;
-#pragma unroll
-                for (int j = 0; j < NL; ++j) {
-                    const uint32_t v = acc[j] + b[j] + c;
-                    acc[j] = v & Radix<LB>::MASK;
-                    c = v >> LB;
-                }
-                store_row4(tbl, 1, lane, acc);
-#pragma unroll
-                for (int j = 0; j < NL; ++j) b[j] = acc[j];  // x~, the multiplier of phase 2
-                phase = 2;
-                __builtin_amdgcn_s_waitcnt(0);
-            } else if (phase == 2) {
-                store_row4(tbl, e, lane, acc);
-                ++e;
-                __builtin_amdgcn_s_waitcnt(0);
-            } else {  // phase 3: the digit's multiply is done
-                --digit;
-                sq = 0;
-            }
-            if (phase == 2 && e == T) {
-                // table complete: T[0] = R mod p (the Montgomery one), start from the top digit
-                load_limbs(b, one_h);
-                store_row4(tbl, 0, lane, b);
-                load_row4(acc, tbl, digit_of(dexp, SH, NW - 1, win), lane);
-                __builtin_amdgcn_s_waitcnt(0);
-                phase = 3;
-            }
-            if (phase == 3 && digit < 0) {
+            } else {  // trailing zero bits done
 #pragma unroll
                 for (int j = 0; j < NL; ++j) b[j] = j == 0 ? 1u : 0u;
                 phase = 4;
             }
         }
+        mont_mul<NL, LB>(acc, acc, b, n, n0);
+        if (phase == 4) break;
+        if (phase == 0) {
+            store_row4(tbl, 1, lane, acc);
+            load_row4(acc, tbl, 0, lane);
+            load_limbs(b, hr + G.h_rrr);
+            phase = 1;
+            // table-building steps leave nothing in flight: the wait the
+            // compiler puts where the window loop joins them would otherwise
+            // also wait for the window's prefetch
+            __builtin_amdgcn_s_waitcnt(0);
+            continue;
+        }
+        if (phase == 1) {
+            load_row4(b, tbl, 1, lane);
+            uint32_t c = 0;
+#pragma unroll
+            for (int j = 0; j < NL; ++j) {
+                const uint32_t v = acc[j] + b[j] + c;
+                acc[j] = v & Radix<LB>::MASK;
+                c = v >> LB;
+            }
+            store_row4(tbl, 0, lane, acc);
+#pragma unroll
+            for (int j = 0; j < NL; ++j) b[j] = acc[j];  // next: x~ x~
+            phase = 2;
+            __builtin_amdgcn_s_waitcnt(0);
+            continue;
+        }
+        if (phase == 2) {
+#pragma unroll
+            for (int j = 0; j < NL; ++j) b[j] = acc[j];  // x~^2, the multiplier of phase 5
+            load_row4(acc, tbl, 0, lane);
+            phase = 5;
+            __builtin_amdgcn_s_waitcnt(0);
+            continue;
+        }
+        if (phase == 5) {
+            store_row4(tbl, e, lane, acc);
+            ++e;
+            __builtin_amdgcn_s_waitcnt(0);
+            if (e < TH) continue;
+            // table complete: the first window starts at the top set bit
+            // (no squarings of 1); d = 0 gives the Montgomery one
+            const int top = exp_top_bit(dexp, SH);
+            if (top < 0) {
+                load_limbs(acc, one_h);
+                st = WinStep::make(0, 0u, false, -1);
+            } else {
+                st = win_first(nx, dexp, SH, top, win);
+                load_row4(acc, tbl, st.idx(), lane);
+                win_advance(st, nx, dexp, SH, win);
+            }
+            __builtin_amdgcn_s_waitcnt(0);
+            phase = 3;
+            sq = 0;
+            continue;
+        }
+        // phase 3: the step's product is done
+        win_advance(st, nx, dexp, SH, win);
+        sq = 0;
     }
     canonicalize<NL, LB>(acc, n);
-    uint32_t *dst = r.half + ((size_t)jt * NL) * kTile + lane;
+    uint32_t *dst = r.half + ((size_t)jt * half_stride(CB)) * kTile + lane;
 #pragma unroll
     for (int j = 0; j < NL; ++j) dst[(size_t)j * kTile] = acc[j];
 }
@@ -886,7 +805,7 @@ PMK_DEV void halves_joint_unit(const ClassRun r, uint32_t jt, uint32_t *tbl, uin
         sq = 0;
     }
     canonicalize<NL, LB>(acc, n);
-    uint32_t *dst = r.half + ((size_t)jt * NL) * kTile + lane;
+    uint32_t *dst = r.half + ((size_t)jt * half_stride(CB)) * kTile + lane;
 #pragma unroll
     for (int j = 0; j < NL; ++j) dst[(size_t)j * kTile] = acc[j];
 }
@@ -1155,7 +1074,7 @@ PMK_DEV void halves_lanes_unit(const ClassRun r, uint32_t u, uint32_t *tbl, uint
     canonicalize_lanes<K, LB, L>(acc, n, pos);
     // the result is below p: limbs from nlh up are zero and not stored (the
     // half buffer holds nlh limbs per number)
-    uint32_t *dst = r.half + ((size_t)(2 * tile + h) * G.nlh + pos * K) * kTile + c;
+    uint32_t *dst = r.half + ((size_t)(2 * tile + h) * half_stride(CB) + pos * K) * kTile + c;
 #pragma unroll
     for (int j = 0; j < K; ++j)
         if (NLT == G.nlh || pos * K + j < G.nlh) dst[(size_t)j * kTile] = acc[j];
@@ -1334,18 +1253,25 @@ PMK_DEV void halves_lanes_joint_unit(const ClassRun r, uint32_t u, uint32_t *tbl
     }
     canonicalize_lanes<K, LB, L>(acc, n, pos);
     // below p: limbs from nlh up are zero and not stored (nlh limbs per number)
-    uint32_t *dst = r.half + ((size_t)(2 * tile + h) * G.nlh + pos * K) * kTile + c;
+    uint32_t *dst = r.half + ((size_t)(2 * tile + h) * half_stride(CB) + pos * K) * kTile + c;
 #pragma unroll
     for (int j = 0; j < K; ++j)
         if (NLT == G.nlh || pos * K + j < G.nlh) dst[(size_t)j * kTile] = acc[j];
 }
+
+}  // namespace pmk
+
+#include "halves_fold.hpp"
+#include "halves_group.hpp"
+
+namespace pmk {
 
 // ------------------------------------------------------------------ per-class kernels
 // Persistent grids: block b owns table slot b and walks units b, b + grid, ...
 template <int CB>
 constexpr int kEncWaves = 2;
 template <int CB>
-constexpr int kDecWaves = (make_geom(CB).nlh > 40 || lanes_half(CB) > 1) ? 2 : 3;
+constexpr int kDecWaves = fold_lane(CB).nl ? fold_lane_waves(CB) : (lanes_half(CB) > 1 ? 2 : 3);
 
 template <int CB>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kEncWaves<CB>))) void encrypt_kernel(
@@ -1390,19 +1316,28 @@ __global__ __launch_bounds__(64) void halves_lanes_joint_kernel(ClassRun r, uint
     for (uint32_t u = u_begin + blockIdx.x; u < u_end; u += gridDim.x) halves_lanes_joint_unit<CB, L>(r, u, tbl, lds);
 }
 
+// units [u_begin, u_end) of the class's own form (fold form: halves_fold_block;
+// job tiles 2 t + h for one lane per number, lane-group units for the
+// 6144/8192-bit classes)
 template <int CB>
-// units [u_begin, u_end) of the class's own form (job tiles 2 t + h for one
-// lane per number, lane-group units for the 6144/8192-bit classes)
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kDecWaves<CB>))) void halves_kernel(
-    ClassRun r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end) {
+constexpr int kDecBlock = fold_lane(CB).nl ? 64 * fold_lane_block(CB) : 64;
+template <int CB>
+__global__ __launch_bounds__(kDecBlock<CB>) __attribute__((amdgpu_waves_per_eu(kDecWaves<CB>))) void halves_kernel(
+    ClassRun r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end, bool split) {
     code_align<code_id(kCodeHalves, CB, 0)>();
-    uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
-    __shared__ uint32_t lds[lds_words_dec<CB>()];
-    for (uint32_t u = u_begin + blockIdx.x; u < u_end; u += gridDim.x) {
-        if constexpr (lanes_half(CB) > 1)
-            halves_lanes_unit<CB>(r, u, tbl, lds);
-        else
-            halves_unit<CB>(r, u, tbl, lds);
+    if constexpr (fold_lane(CB).nl != 0) {
+        __shared__ __align__(16) uint32_t table[FoldHalves<CB>::WORDS];
+        __shared__ __align__(16) uint32_t entry[fold_lane_prefetch(CB) ? fold_lane_block(CB) * FoldHalves<CB>::ROW4 : 4];
+        halves_fold_block<CB>(r, slot_words, u_begin, u_end, split, table, entry);
+    } else {
+        uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
+        __shared__ uint32_t lds[lds_words_dec<CB>()];
+        for (uint32_t u = u_begin + blockIdx.x; u < u_end; u += gridDim.x) {
+            if constexpr (lanes_half(CB) > 1)
+                halves_lanes_unit<CB>(r, u, tbl, lds);
+            else
+                halves_unit<CB>(r, u, tbl, lds);
+        }
     }
 }
 
@@ -1435,8 +1370,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(make_geom(CB
     const uint32_t *kr = keys + (size_t)desc[slot].key * G.stride;
     const uint32_t *hp = kr + G.off_half[0];
     const uint32_t *hq = kr + G.off_half[1];
-    const uint32_t *mp_src = half + ((size_t)(2 * tile) * NL) * CPT + c;
-    const uint32_t *mq_src = half + ((size_t)(2 * tile + 1) * NL) * CPT + c;
+    const uint32_t *mp_src = half + ((size_t)(2 * tile) * half_stride(CB)) * CPT + c;
+    const uint32_t *mq_src = half + ((size_t)(2 * tile + 1) * half_stride(CB)) * CPT + c;
 
     uint32_t p[NL], mq[NL], a[NL], b[NL];
     load_limbs(p, hp + G.h_m);
@@ -1516,8 +1451,8 @@ __global__ __launch_bounds__(kGarnerLdsSlots) void garner_lds_kernel(const uint3
     }
     const uint32_t n0 = hp[G.h_m0];
     __syncthreads();
-    const uint32_t *mp_src = half + ((size_t)(2 * tile) * NL) * CPT + c;
-    const uint32_t *mq_src = half + ((size_t)(2 * tile + 1) * NL) * CPT + c;
+    const uint32_t *mp_src = half + ((size_t)(2 * tile) * half_stride(CB)) * CPT + c;
+    const uint32_t *mq_src = half + ((size_t)(2 * tile + 1) * half_stride(CB)) * CPT + c;
     {
         // a = m_p + p - m_q, in (0, 2p)
         int32_t cy = 0;

@@ -1,11 +1,7 @@
-// CRT halves in lane groups (halves_lanes_kernel) for the part of a launch
-// that leaves SIMDs idle: the one-lane classes (128- to 4096-bit keys) with 2
-// or 4 lanes per number for the last partial round of a launch and for
-// launches too small to fill the chip, the lane-group classes (6144/8192) with
-// 8 instead of 4 for small launches.  There a wave per 64 (or 16) numbers
-// leaves most SIMDs with one wave or none, while L lanes per number give more
-// waves, each with a shorter dependency chain per product.  A translation unit of its own, so the
-// per-class objects stay as they are.
+// CRT halves in lane groups (halves_lanes_kernel) of the 128- to 512-bit classes
+// for the part of a launch that leaves SIMDs idle: 2 or 4 lanes per number give
+// more waves, each with a shorter dependency chain per product.  A translation
+// unit of its own, so the per-class objects stay as they are.
 #include "kernels_impl.hpp"
 
 namespace pmk {
@@ -41,14 +37,8 @@ int launch_class(const ClassRun &r, uint32_t jt_begin, uint32_t jt_end, hipStrea
 
 template <int CB>
 int launch_L(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, hipStream_t s) {
-    if constexpr (lanes_half(CB) == 1) {
-        if (L == 2) return launch_class<CB, 2>(r, jt_begin, jt_end, s);
-        if (L == 4) return launch_class<CB, 4>(r, jt_begin, jt_end, s);
-        if constexpr (eight_lanes(CB))
-            if (L == 8) return launch_class<CB, 8>(r, jt_begin, jt_end, s);
-    } else {
-        if (L == 2 * lanes_half(CB)) return launch_class<CB, 2 * lanes_half(CB)>(r, jt_begin, jt_end, s);
-    }
+    if (L == 2) return launch_class<CB, 2>(r, jt_begin, jt_end, s);
+    if (L == 4) return launch_class<CB, 4>(r, jt_begin, jt_end, s);
     return (int)hipErrorInvalidValue;
 }
 
@@ -74,19 +64,6 @@ uint32_t lanes_resident(int cls, int L) {
         case 1 * 16 + 4: return resident_of<256, 4>();
         case 2 * 16 + 2: return resident_of<512, 2>();
         case 2 * 16 + 4: return resident_of<512, 4>();
-        case 3 * 16 + 2: return resident_of<1024, 2>();
-        case 3 * 16 + 4: return resident_of<1024, 4>();
-        case 4 * 16 + 2: return resident_of<2048, 2>();
-        case 4 * 16 + 4: return resident_of<2048, 4>();
-        case 4 * 16 + 8: return resident_of<2048, 8>();
-        case 5 * 16 + 2: return resident_of<3072, 2>();
-        case 5 * 16 + 4: return resident_of<3072, 4>();
-        case 5 * 16 + 8: return resident_of<3072, 8>();
-        case 6 * 16 + 2: return resident_of<4096, 2>();
-        case 6 * 16 + 4: return resident_of<4096, 4>();
-        case 6 * 16 + 8: return resident_of<4096, 8>();
-        case 7 * 16 + 2 * lanes_half(6144): return resident_of<6144, 2 * lanes_half(6144)>();
-        case 8 * 16 + 2 * lanes_half(8192): return resident_of<8192, 2 * lanes_half(8192)>();
         default: return 0;
     }
 }
@@ -98,12 +75,6 @@ int launch_halves_lanes(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt
         case 0: return launch_L<128>(r, L, jt_begin, jt_end, s);
         case 1: return launch_L<256>(r, L, jt_begin, jt_end, s);
         case 2: return launch_L<512>(r, L, jt_begin, jt_end, s);
-        case 3: return launch_L<1024>(r, L, jt_begin, jt_end, s);
-        case 4: return launch_L<2048>(r, L, jt_begin, jt_end, s);
-        case 5: return launch_L<3072>(r, L, jt_begin, jt_end, s);
-        case 6: return launch_L<4096>(r, L, jt_begin, jt_end, s);
-        case 7: return launch_L<6144>(r, L, jt_begin, jt_end, s);
-        case 8: return launch_L<8192>(r, L, jt_begin, jt_end, s);
         default: return (int)hipErrorNotSupported;
     }
 }

@@ -54,9 +54,9 @@ int noalloc_keys(pmk_ctx *ctx) {
     ctx->na_count.assign(nk, 0);
     ctx->na_tile.assign(nk, 0);
     // padded slots over all classes <= chunks + 63 per key; per class two
-    // aligned arrays (descriptors, one tile key per 64 slots) after the error word
+    // aligned arrays (descriptors, one tile key and at most one group per 64 slots) after the error word
     const uint64_t slots = kNoAllocMaxChunks + (uint64_t)(kTile - 1) * nk;
-    const uint64_t need = kAlign + slots * (sizeof(ChunkDesc) + sizeof(uint32_t)) + 2 * kAlign * kNumClasses;
+    const uint64_t need = kAlign + slots * (sizeof(ChunkDesc) + 2 * sizeof(uint32_t)) + 2 * kAlign * kNumClasses;
     if (need > ctx->na_host_bytes) {
         if (ctx->na_host) (void)hipHostFree(ctx->na_host);
         ctx->na_host = nullptr;
@@ -117,7 +117,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         off_desc[c] = o;
         o += align_up((uint64_t)tiles[c] * kTile * sizeof(ChunkDesc));
         off_tk[c] = o;
-        o += align_up((uint64_t)tiles[c] * sizeof(uint32_t));
+        o += align_up(2ull * tiles[c] * sizeof(uint32_t));  // and the groups
     }
     const uint64_t prefix = o;
     for (int c = 0; c < kNumClasses; ++c) {
@@ -128,7 +128,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         off_y[c] = o;
         o += align_up((uint64_t)tiles[c] * g.S * kTile * 4);
         off_h[c] = o;
-        o += align_up((uint64_t)tiles[c] * 2 * g.nlh * kTile * 4);
+        o += align_up((uint64_t)tiles[c] * 2 * half_stride(kClassBits[c]) * kTile * 4);
     }
     if (prefix > ctx->na_host_bytes || o >= kNoAllocScratchBytes)
         return set_err(ctx, PMK_ESIZE, "the chunks need %llu bytes of scratch, the static scratch holds %llu",
@@ -141,7 +141,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         if (!tiles[c]) continue;
         const uint64_t slot_bytes = table_words_per_slot(c, 1, ctx->win[c]) * 4;
         const uint64_t fit = share / slot_bytes;
-        slots[c] = (uint32_t)std::min<uint64_t>({fit, wave_slots(c, 1, ctx->num_cus), exp_units(c, 1, tiles[c])});
+        slots[c] = (uint32_t)std::min<uint64_t>({fit, wave_slots(c, 1, ctx->num_cus), table_units(c, tiles[c])});
         if (!slots[c])
             return set_err(ctx, PMK_ESIZE, "no room left in the static scratch for a %d-bit window table",
                            kClassBits[c]);
@@ -160,6 +160,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
                           d[(uint64_t)ctx->na_tile[k] * kTile + ctx->na_count[k]++] =
                               ChunkDesc{off, ct, ks.slot, (uint32_t)len};
                       });
+    uint32_t ngroups[kNumClasses] = {}, parts[kNumClasses] = {}, most[kNumClasses] = {};
     for (uint32_t k = 0; k < nk; ++k) {
         const uint32_t n = ctx->na_count[k];
         if (!n) continue;
@@ -168,6 +169,16 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         uint32_t *tk = (uint32_t *)(h + off_tk[ks.cls]) + ctx->na_tile[k];
         const uint32_t nt = (n + kTile - 1) / kTile;
         for (uint32_t t = 0; t < nt; ++t) tk[t] = ks.slot;
+        parts[ks.cls] += (n + 15) / 16;
+        // groups of this key's tiles, as tile_groups makes them
+        uint32_t *groups = (uint32_t *)(h + off_tk[ks.cls]) + tiles[ks.cls];
+        const uint32_t per = (uint32_t)fold_lane_block(kClassBits[ks.cls]);
+        for (uint32_t t = 0, g = (nt + per - 1) / per; t < nt; --g) {
+            const uint32_t m = (nt - t + g - 1) / g;
+            groups[ngroups[ks.cls]++] = (ctx->na_tile[k] + t) | (m - 1) << 30;
+            most[ks.cls] = std::max(most[ks.cls], m);
+            t += m;
+        }
         for (uint32_t i = n; i < nt * kTile; ++i) d[i] = ChunkDesc{0, 0, ks.slot, 0};  // padding slots
     }
     if (hipSetDevice(ctx->device) != hipSuccess) return set_err(ctx, PMK_EDEVICE, "hipSetDevice failed");
@@ -186,11 +197,17 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         r.keys = ctx->d_keys[c];
         r.desc = (const ChunkDesc *)(base + off_desc[c]);
         r.tile_key = (const uint32_t *)(base + off_tk[c]);
+        r.groups = r.tile_key + tiles[c];
+        r.ngroups = ngroups[c];
+        r.group_tiles = most[c];
+        r.parts = parts[c];
+        r.fold = ctx->d_fold[c];
         r.x32 = (uint32_t *)(base + off_x[c]);
         r.y32 = (uint32_t *)(base + off_y[c]);
         r.half = (uint32_t *)(base + off_h[c]);
         r.table = (uint32_t *)(base + off_t[c]);
         r.slots_dec = slots[c];
+        r.table_words = slots[c] * table_words_per_slot(c, 1, ctx->win[c]);
         r.slots_enc = 0;
         r.err = d_err;
         r.grid_cap = ctx->grid_limit;

@@ -110,10 +110,10 @@ hipError_t ensure_tables(pmk_plan *pl) {
         r.grid_cap = pl->ctx->grid_limit;
         r.fill_lanes = pl->ctx->fill_lanes[c];
         r.tail_lanes = pl->ctx->tail_lanes[c];
-        const uint64_t need = std::max(r.slots_enc * table_words_per_slot(c, 0, 0),
-                                       r.slots_dec * table_words_per_slot(c, 1, r.win));
+        const uint64_t need = table_words(c, r.slots_enc, r.slots_dec, r.ntiles, r.win);
         const hipError_t e = regrow(pl, &r.table, pl->table_cap[c], need);
         if (e != hipSuccess) return e;
+        r.table_words = pl->table_cap[c];
     }
     return hipSuccess;
 }
@@ -157,6 +157,8 @@ void pmk_destroy(pmk_ctx *ctx) {
     (void)hipSetDevice(ctx->device);
     while (!ctx->plans.empty()) pmk_plan_destroy(*ctx->plans.begin());
     for (auto &p : ctx->d_keys)
+        if (p) (void)hipFree(p);
+    for (auto &p : ctx->d_fold)
         if (p) (void)hipFree(p);
     if (ctx->mr_table) (void)hipFree(ctx->mr_table);
     for (auto &p : ctx->d_mp_keys)
@@ -205,20 +207,32 @@ int pmk_keys_load(pmk_ctx *ctx, const pmk_key *keys, uint32_t nkeys) {
     }
     if (hipSetDevice(ctx->device) != hipSuccess) return set_err(ctx, PMK_EDEVICE, "hipSetDevice failed");
     uint32_t *fresh[kNumClasses] = {};
-    for (int c = 0; c < kNumClasses; ++c) {
+    uint8_t *fold[kNumClasses] = {};
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < kNumClasses && e == hipSuccess; ++c) {
         if (!counts[c]) continue;
         const size_t bytes = host[c].size() * sizeof(uint32_t);
-        hipError_t e = hipMalloc(&fresh[c], bytes);
+        e = hipMalloc(&fresh[c], bytes);
         if (e == hipSuccess) e = hipMemcpy(fresh[c], host[c].data(), bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            for (auto &p : fresh)
-                if (p) (void)hipFree(p);
-            return hip_err(ctx, e, "key table upload");
-        }
+        const uint64_t fb = fold_bytes_per_key(c) * counts[c];
+        if (e != hipSuccess || !fb) continue;
+        e = hipMalloc(&fold[c], fb);
+        if (e == hipSuccess) e = hipMemset(fold[c], 0, fb);
+        if (e == hipSuccess) e = (hipError_t)launch_fold_setup(c, fresh[c], counts[c], fold[c], nullptr);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) {
+        for (auto &p : fresh)
+            if (p) (void)hipFree(p);
+        for (auto &p : fold)
+            if (p) (void)hipFree(p);
+        return hip_err(ctx, e, "key table upload");
     }
     for (int c = 0; c < kNumClasses; ++c) {
         if (ctx->d_keys[c]) (void)hipFree(ctx->d_keys[c]);
+        if (ctx->d_fold[c]) (void)hipFree(ctx->d_fold[c]);
         ctx->d_keys[c] = fresh[c];
+        ctx->d_fold[c] = fold[c];
         ctx->class_count[c] = counts[c];
     }
     ctx->keys.swap(slots);
@@ -261,12 +275,13 @@ int pmk_plan_create(pmk_ctx *ctx, const uint32_t *key_map, uint64_t nchunks, uin
     // the tile's key and have msg_len 0
     std::vector<std::vector<ChunkDesc>> per(kNumClasses);
     std::vector<std::vector<uint32_t>> tkeys(kNumClasses);
-    uint32_t counts[kNumClasses] = {};
+    uint32_t counts[kNumClasses] = {}, parts[kNumClasses] = {};
     for (size_t k = 0; k < per_key.size(); ++k) {
         const auto &list = per_key[k];
         const int c = ctx->keys[k].cls;
         const size_t cpt = (size_t)chunks_per_tile(kClassBits[c]);
         counts[c] += (uint32_t)list.size();
+        parts[c] += (uint32_t)((list.size() + 15) / 16);
         for (size_t i = 0; i < list.size(); i += cpt) {
             tkeys[c].push_back(ctx->keys[k].slot);
             for (size_t l = 0; l < cpt; ++l)
@@ -290,6 +305,7 @@ int pmk_plan_create(pmk_ctx *ctx, const uint32_t *key_map, uint64_t nchunks, uin
         ClassRun &r = pl->runs[c];
         r.cls = c;
         r.count = counts[c];
+        r.parts = parts[c];
         r.ntiles = (uint32_t)tkeys[c].size();
         r.err = pl->d_err;
         r.win = ctx->win[c];
@@ -298,7 +314,13 @@ int pmk_plan_create(pmk_ctx *ctx, const uint32_t *key_map, uint64_t nchunks, uin
         const uint64_t tiles = r.ntiles, cpt = (uint64_t)chunks_per_tile(kClassBits[c]);
         r.keys = ctx->d_keys[c];
         r.slots_enc = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 0, ctx->num_cus), exp_units(c, 0, r.ntiles)));
-        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), exp_units(c, 1, r.ntiles)));
+        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(c, r.ntiles)));
+        r.fold = ctx->d_fold[c];
+        // the tiles' keys, then the groups of tiles under one key
+        std::vector<uint32_t> &tkp = tkeys[c];
+        tkp.reserve(2 * tkp.size());
+        r.group_tiles = tile_groups(std::vector<uint32_t>(tkp), r.ntiles, fold_lane_block(kClassBits[c]), tkp);
+        r.ngroups = (uint32_t)tkp.size() - r.ntiles;
         ChunkDesc *d = nullptr;
         uint32_t *tk = nullptr;
         e = dev_alloc(pl, &d, per[c].size() * sizeof(ChunkDesc));
@@ -309,9 +331,10 @@ int pmk_plan_create(pmk_ctx *ctx, const uint32_t *key_map, uint64_t nchunks, uin
             e = hipMemcpy(tk, tkeys[c].data(), tkeys[c].size() * sizeof(uint32_t), hipMemcpyHostToDevice);
         r.desc = d;
         r.tile_key = tk;
+        r.groups = tk + r.ntiles;
         if (e == hipSuccess) e = dev_alloc(pl, &r.x32, tiles * g.S * cpt * sizeof(uint32_t));
         if (e == hipSuccess) e = dev_alloc(pl, &r.y32, tiles * g.S * cpt * sizeof(uint32_t));
-        if (e == hipSuccess) e = dev_alloc(pl, &r.half, tiles * 2 * g.nlh * cpt * sizeof(uint32_t));
+        if (e == hipSuccess) e = dev_alloc(pl, &r.half, tiles * 2 * half_stride(kClassBits[c]) * cpt * sizeof(uint32_t));
     }
     if (e == hipSuccess) e = ensure_tables(pl);
     if (e != hipSuccess) {
@@ -446,8 +469,9 @@ int pmk_decrypt_blinded_plan(pmk_plan *pl, const uint8_t *d_ct_star, const uint8
         ClassRun &r = pl->runs[c];
         if (!r.ntiles) continue;
         // the one-pass form keeps two odd-power tables per slot
-        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], 2 * r.slots_dec * table_words_per_slot(c, 1, r.win));
+        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], 2 * table_words(c, 0, r.slots_dec, r.ntiles, r.win));
         if (te != hipSuccess) return hip_err(ctx, te, "window table allocation");
+        r.table_words = pl->table_cap[c];
     }
     for (int c = 0; c < kNumClasses; ++c) {
         const ClassRun &r = pl->runs[c];
@@ -541,31 +565,34 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
     a.slot_words = batch_slot_words();
     int e = 0;
     if (!decrypt && total) e = launch_counter_reset(pl->d_counter, stream);
-    // launches of the exponentiation stage: (class, stream index)
+    // classes of the exponentiation stage: decryption by canonical work, largest
+    // first; encryption the classes outside the work queue, largest moduli first
     int order[kNumClasses], nl = 0;
-    for (int c = kNumClasses - 1; c >= 0 && !e; --c) {
-        ClassRun r = pl->runs[c];
-        if (!r.ntiles) continue;
-        e = timed_launch(pl, PMK_KERNEL_PACK, stream, [&] { return launch_pack(r, in, decrypt, stream); });
-        if (decrypt || !is_wide_class(c)) order[nl++] = c;
-    }
-    if (decrypt) {  // classes by canonical work, largest first
+    for (int c = kNumClasses - 1; c >= 0; --c)
+        if (pl->runs[c].ntiles && (decrypt || !is_wide_class(c))) order[nl++] = c;
+    auto pack = [&](int c, void *s) {
+        return timed_launch(pl, PMK_KERNEL_PACK, s, [&] { return launch_pack(pl->runs[c], in, decrypt, s); });
+    };
+    int lanes = total && nl ? 2 : 1;
+    if (decrypt) {
         auto work = [&](int c) {
             const double s = kClassBits[c] / 64.0;
             return (double)pl->runs[c].ntiles * kClassBits[c] * (2 * s * s + s);
         };
         std::sort(order, order + nl, [&](int x, int y) { return work(x) > work(y); });
+        lanes = std::min(nl, 3);  // one side stream measured 5 ms more (58.3 / 53.0 ms at 25 MiB in 4 classes)
+    } else {
+        for (int c = kNumClasses - 1; c >= 0 && !e; --c)
+            if (pl->runs[c].ntiles) e = pack(c, stream);
     }
-    // decryption: the two largest classes on streams of their own, the rest one
-    // after another on a third (measured on the mixed 25 MiB workload: 60.7
-    // against 61.8 ms with every class on a stream of its own, 65.0 ms with the
-    // largest class alone beside all others)
-    const int lanes = decrypt ? std::min(nl, 3) : (total && nl ? 2 : 1);
     if (!e && lanes > 1) {
         e = hipEventRecord(pl->fork_event, (hipStream_t)stream);
         for (int i = 0; i < lanes - 1 && !e; ++i) e = hipStreamWaitEvent(pl->side_stream[i], pl->fork_event, 0);
     }
     auto stream_of = [&](int lane) { return lane == 0 ? stream : (void *)pl->side_stream[lane - 1]; };
+    // the largest class's packing and halves on `stream`, the others on the side
+    // streams, packed meanwhile, so that its blocks are placed first
+    for (int i = 0; i < nl && decrypt && !e; ++i) e = pack(order[i], stream_of(i < lanes ? i : lanes - 1));
     if (!e && !decrypt && total) {
         void *s = stream_of(lanes - 1);
         const uint32_t grid = persistent_grid(total, pl->batch_slots, ctx->grid_limit);
@@ -575,13 +602,13 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
         ClassRun r = pl->runs[order[i]];
         r.win = ctx->win[order[i]];
         if (decrypt && nl > 1) {
-            // classes side by side fill the chip together: no class's launch is
-            // short of work on its own, so every number keeps one lane
-            // (measured: lane groups here cost 47 % on the mixed 25 MiB workload)
-            // and a class's last partial round stays in its launch, where its
-            // waves start as soon as waves of that launch finish
-            r.fill_lanes = lanes_half(kClassBits[order[i]]);
-            r.tail_lanes = lanes_half(kClassBits[order[i]]) > 1 ? r.fill_lanes : 0;
+            // classes side by side share the chip (group_launch); one lane per
+            // number otherwise, since together they fill it, and a class's last
+            // partial round stays in its launch, where its waves start as soon as
+            // waves of that launch finish
+            r.share = (uint32_t)nl;
+            if (!fold_group(kClassBits[order[i]]).nl) r.fill_lanes = 1;
+            r.tail_lanes = 0;
         }
         void *s = decrypt ? stream_of(i < lanes ? i : lanes - 1) : stream;
         e = timed_launch(pl, decrypt ? PMK_KERNEL_CRT_HALVES : PMK_KERNEL_ENCRYPT, s, [&] {
@@ -938,6 +965,8 @@ int pmk_autotune(pmk_ctx *ctx, const char *cache_path, int flags) {
                 int lpick = 1;
                 for (int L : {1, 2, 4, 8}) {
                     if (L == 8 && (which == 1 || !eight_lanes(cb))) continue;  // fill only, where supported
+                    // with a group form: one lane, or that form (any other count)
+                    if (fold_group(cb).nl && L != 1 && (which == 1 || L != default_fill_lanes(cb))) continue;
                     (void)pmk_set_lanes(ctx, (uint32_t)cb, which == 0 ? L : best_fill, which == 0 ? best_tail : L);
                     float ms = 0.f;
                     rc = tune_batch(ctx, k0, sizes[which], st, 3, &ms);

@@ -147,20 +147,103 @@ struct ChunkDesc {
 
 constexpr int kTile = 64;  // bignums per wavefront
 
+// Forms of the CRT halves whose reduction runs on the matrix cores (fold.hpp):
+// numbers of nl limbs of lb bits (nl 0: the class has no such form), F = lb nl
+// at least 17 bits above the class's largest prime, so that the folded sum stays
+// well below 2^F.
+struct FoldForm {
+    int lb, nl;
+};
+// a number in one lane (launches that fill the chip)
+PMK_HD constexpr FoldForm fold_lane(int bits) {
+    switch (bits) {
+        case 1024: return {28, 20};
+        case 2048: return {29, 36};
+        case 3072: return {28, 56};
+        case 4096: return {28, 76};
+        default: return {0, 0};
+    }
+}
+// its waves per block (tiles of one key that share the prime's table in LDS:
+// 7, 21, 51 and 94 KB) and per SIMD (limited by registers: 76 limbs take the
+// whole file), and whether a window's entry is copied into LDS ahead of its
+// product (where the table leaves room)
+PMK_HD constexpr int fold_lane_block(int bits) { return bits >= 3072 ? 4 : 2; }
+PMK_HD constexpr int fold_lane_waves(int bits) { return bits >= 4096 ? 1 : (bits >= 2048 ? 2 : 3); }
+PMK_HD constexpr bool fold_lane_prefetch(int bits) { return bits <= 2048; }
+// a number spread over a block (small launches; the classes above); nl a
+// multiple of 4, LB = 28: limbs there carry up to twice 2^lb
+PMK_HD constexpr FoldForm fold_group(int bits) {
+    switch (bits) {
+        case 1024: return {28, 20};
+        case 2048: return {28, 40};
+        case 3072: return {28, 56};
+        case 4096: return {28, 76};
+        case 6144: return {28, 112};
+        case 8192: return {28, 148};
+        default: return {0, 0};
+    }
+}
+// K steps of 64 digits of its MFMAs, and how many of them stay in registers
+PMK_HD constexpr int fold_group_steps(int bits) { return (4 * fold_group(bits).nl + 63) / 64; }
+PMK_HD constexpr int fold_group_resident(int bits) { return bits > 6144 ? 3 : (bits > 4096 ? 5 : 16); }
+PMK_HD constexpr int fold_group_waves(int) { return 2; }  // waves per SIMD
+// waves per block
+PMK_HD constexpr int fold_group_block(int bits) { return bits <= 1024 ? 1 : (bits <= 2048 ? 2 : (bits <= 4096 ? 4 : (bits <= 6144 ? 7 : 8))); }
+// limbs per number of the half buffer: a fold result, or the canonical half
+PMK_HD constexpr int half_stride(int bits) {
+    const int nlh = make_geom(bits).nlh, a = fold_lane(bits).nl, b = fold_group(bits).nl;
+    return a > nlh ? (a > b ? a : b) : (b > nlh ? b : nlh);
+}
+// Table of one prime (byte offsets): per form the 4 nl start values of the
+// accumulators, then the digits of W in operand order.
+struct FoldTable {
+    uint32_t lane, group, size;
+};
+PMK_HD constexpr uint32_t fold_lane_bytes(FoldForm f) { return 16u * f.nl + 16u * f.nl * f.nl; }
+PMK_HD constexpr FoldTable fold_table(int bits) {
+    FoldTable t{};
+    t.lane = 0;
+    t.group = (uint32_t)round_up((int)fold_lane_bytes(fold_lane(bits)), 256);
+    const uint32_t nl = (uint32_t)fold_group(bits).nl;
+    t.size = t.group + (uint32_t)round_up((int)(16 * nl + nl / 4 * fold_group_steps(bits) * 1024), 256);
+    return t;
+}
+// Bias of a result row, digit j of limb k: at or above the largest sum of 4 nl
+// products of a digit of t_hi with a digit of W < 2^p; a power of two, 0 for rows
+// that W does not reach.  Digits of t_hi are at most 128 in size, the top one of
+// a limb 2^(lb - 24) + 1 (2^(lb - 23) + 1 where limbs carry up to twice 2^lb).
+PMK_HD constexpr uint32_t fold_bias(FoldForm f, int p, int k, int j, bool loose) {
+    const int nb = p - f.lb * k < f.lb ? p - f.lb * k : f.lb;  // bits of W in limb k
+    if (nb < 8 * j || nb <= 0) return 0;
+    const uint64_t w = nb >= 8 * j + 8 && j < 3 ? 128 : (1ull << (nb - 8 * j)) + 1;
+    const uint64_t most = (uint64_t)f.nl * (3 * 128 + (1u << (f.lb - (loose ? 23 : 24))) + 2) * w;
+    uint64_t b = 1;
+    while (b < most) b <<= 1;
+    return (uint32_t)b;
+}
+
 // Arguments of one class's launches inside a plan.
 struct ClassRun {
     int cls;                   // index into kClassBits
     uint32_t count;            // chunks of this class
+    uint32_t parts;            // groups of up to 16 of them under one key
+    uint32_t share;            // classes whose launches run beside this one's (0 or 1: none)
     uint32_t ntiles;           // key-uniform tiles of this class
     const uint32_t *keys;      // class key table (device), Geom::stride words per key
     const ChunkDesc *desc;     // ntiles * cpt slot descriptors (device)
     const uint32_t *tile_key;  // ntiles key records (device)
+    const uint32_t *groups;    // fold form: ngroups groups of tiles under one key, the first tile and
+    uint32_t ngroups;          // the tiles after it in bits 30 and 31 (device);
+    uint32_t group_tiles;      // tiles of the largest
+    const uint8_t *fold;       // fold tables of the class's keys (two primes each, fold_table)
     uint32_t *x32;             // [tile][word < S][chunk < cpt]: packed input words
     uint32_t *y32;             // same shape: result words before unpacking
-    uint32_t *half;            // [tile][p, q][limb < nlh][chunk < cpt]: CRT half results
+    uint32_t *half;            // [tile][p, q][limb < half_stride][chunk < cpt]: CRT half results
     uint32_t *table;           // per resident wave: window table scratch
     uint32_t slots_enc;        // wave slots in `table` for the encryption kernel
     uint32_t slots_dec;        // wave slots in `table` for the CRT-halves kernel
+    uint64_t table_words;      // words of `table`
     uint32_t *err;             // device error word: bit 0 block out of range, bit 1 blinding factor not invertible
     uint8_t *slot_err;         // optional, per descriptor slot: 1 where unpacking rejected the chunk
     uint32_t grid_cap;         // 0, or the most resident waves a persistent launch may use
@@ -229,6 +312,28 @@ int launch_pack(const ClassRun &r, const uint8_t *src, int decrypt, void *stream
 int launch_encrypt(const ClassRun &r, void *stream);
 int launch_decrypt_halves(const ClassRun &r, void *stream);
 int launch_garner(const ClassRun &r, void *stream);
+// fold tables of a class's `count` key records (kfold.hip), two per key
+int launch_fold_setup(int cls, const uint32_t *keys, uint32_t count, uint8_t *fold, void *stream);
+inline uint64_t fold_bytes_per_key(int cls) { return 2ull * fold_table(kClassBits[cls]).size; }
+// Groups of up to `per` tiles under one key (ClassRun::groups) of a class's
+// tiles, appended to out: each key's tiles in the fewest groups, of equal sizes up to one.
+// Returns the largest size.
+template <typename Vec>
+uint32_t tile_groups(const Vec &tile_key, uint32_t ntiles, int per, Vec &out) {
+    uint32_t most = 1;
+    for (uint32_t t = 0; t < ntiles;) {
+        uint32_t n = 1;
+        while (t + n < ntiles && tile_key[t + n] == tile_key[t]) ++n;
+        for (uint32_t g = (n + per - 1) / per; n; --g) {
+            const uint32_t k = (n + g - 1) / g;
+            out.push_back(t | (k - 1) << 30);
+            if (k > most) most = k;
+            t += k;
+            n -= k;
+        }
+    }
+    return most;
+}
 // blinded decryption in one pass per prime: half[h] = (c*)^d_h c_R^(p_h-1-d_h) mod p_h
 // with c* at r.x32 and c_R at r.fin32; tables need 2 table_words_per_slot(cls, 1, win)
 // words per slot
@@ -309,6 +414,43 @@ uint64_t table_words_per_slot(int cls, int decrypt, int win);
 uint32_t wave_slots(int cls, int decrypt, int num_cus);
 // work units (wavefronts' worth of bignums) of the exponentiation kernels
 uint32_t exp_units(int cls, int decrypt, uint32_t ntiles);
+// table slots (waves) a class's CRT-halves launch over ntiles tiles can use
+uint32_t table_units(int cls, uint32_t ntiles);
+// CRT halves of a whole launch with numbers spread over blocks (kgroup.hip):
+// table words per block, blocks that are resident, and the launch, which leaves
+// fold results in r.half; launch_halves_group takes the tiles from that of group
+// `first` on (r.groups; 0: all of them)
+uint64_t group_slot_words(int cls, int win);
+uint32_t group_resident(int cls);
+int launch_halves_group(const ClassRun &r, uint32_t first, void *stream);
+// Whether a CRT-halves launch takes that form: while its blocks (2 r.parts, each
+// 16 chunks modulo one prime) are few.  A block's chain is 2 to 5 times shorter
+// than the one-lane chain, but it takes more of the chip per number, so the
+// one-lane form wins once it fills the SIMDs.  Measured, group against one lane:
+//   1024 bits  0.80 / 0.96 ms up to 600 blocks, 1.10 / 1.0 ms at 1,008
+//   2048 bits  3.0 / 3.86 ms at 640 blocks, 5.9 / 4.0 ms at 2,000
+//   3072 bits  3.6 ms to 256 blocks, 4.35 ms more for every 512 / 13.4 ms to 1,024 tiles
+//   4096 bits  6.3 ms to 256 blocks, 8.1 ms more for every 512 / 28.3 ms to 128 groups
+//   6144 and 8192 bits against 4 lanes per number: 16 / 74 and 40 / 164 ms at 190,
+//   about even where the 4-lane form fills the chip
+// The limits lie where the two meet (256 compute units); classes side by side
+// share the chip.
+inline uint64_t group_limit(int bits, uint32_t cus) {
+    switch (bits) {
+        case 1024: return 3ull * cus;
+        case 2048: return 7ull * cus / 2;
+        case 3072: return 13ull * cus / 2;
+        case 4096: return 7ull * cus;
+        default: return ~0ull;
+    }
+}
+inline bool group_launch(const ClassRun &r, uint32_t cus) {
+    const int bits = kClassBits[r.cls];
+    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits)) return false;
+    return 2ull * r.parts * (r.share > 1 ? r.share : 1) <= group_limit(bits, cus);
+}
+// table words that a class's launches over ntiles tiles use
+uint64_t table_words(int cls, uint32_t slots_enc, uint32_t slots_dec, uint32_t ntiles, int win);
 // persistent batched exponentiation (kbatch.hip)
 int launch_batch(const BatchArgs &a, uint32_t grid, void *stream);
 int launch_counter_reset(uint32_t *counter, void *stream);

@@ -35,6 +35,7 @@ struct pmk_ctx {
     std::string err;
     std::vector<KeySlot> keys;
     uint32_t *d_keys[kNumClasses] = {};
+    uint8_t *d_fold[kNumClasses] = {};  // fold tables of the keys (fold_table)
     uint32_t class_count[kNumClasses] = {};
     int live_plans = 0;
     std::set<pmk_plan *> plans;

@@ -200,13 +200,13 @@ hipError_t ensure_class(Server *sv, RoundPlan &R, int c, uint64_t tiles) {
     (void)hipStreamSynchronize(sv->stream);
     hipError_t e = grow_buffer(&R.pl, (void **)&R.desc[c], cap, t * cpt * sizeof(ChunkDesc));
     cap = 0;
-    if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&R.tkey[c], cap, t * sizeof(uint32_t));
+    if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&R.tkey[c], cap, 2 * t * sizeof(uint32_t));
     cap = 0;
     if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&r.x32, cap, t * g.S * cpt * sizeof(uint32_t));
     cap = 0;
     if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&r.y32, cap, t * g.S * cpt * sizeof(uint32_t));
     cap = 0;
-    if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&r.half, cap, t * 2 * g.nlh * cpt * sizeof(uint32_t));
+    if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&r.half, cap, t * 2 * half_stride(kClassBits[c]) * cpt * sizeof(uint32_t));
     cap = 0;
     if (e == hipSuccess) e = grow_buffer(&R.pl, (void **)&R.slot_err[c], cap, t * cpt);
     if (e == hipSuccess) R.cap_tiles[c] = t;
@@ -246,6 +246,7 @@ int launch_round(Server *sv, RoundPlan &R, int decrypt, const std::vector<Taken>
         R.h_req[c].clear();
         R.pl.runs[c].ntiles = 0;
         R.pl.runs[c].count = 0;
+        R.pl.runs[c].parts = 0;
     }
     for (uint32_t k : key_order) {
         const int c = ctx->keys[k].cls;
@@ -253,6 +254,7 @@ int launch_round(Server *sv, RoundPlan &R, int decrypt, const std::vector<Taken>
         const size_t cpt = (size_t)chunks_per_tile(kClassBits[c]);
         const auto &list = per_key[k];
         R.pl.runs[c].count += (uint32_t)list.size();
+        R.pl.runs[c].parts += (uint32_t)((list.size() + 15) / 16);
         for (size_t i = 0; i < list.size(); i += cpt) {
             R.h_tkey[c].push_back(slot);
             for (size_t l = 0; l < cpt; ++l) {
@@ -278,12 +280,16 @@ int launch_round(Server *sv, RoundPlan &R, int decrypt, const std::vector<Taken>
             if (e != hipSuccess) return (int)e;
         }
         r.slots_enc = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 0, ctx->num_cus), exp_units(c, 0, r.ntiles)));
-        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), exp_units(c, 1, r.ntiles)));
+        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(c, r.ntiles)));
+        r.fold = ctx->d_fold[c];
+        r.group_tiles = tile_groups(std::vector<uint32_t>(R.h_tkey[c]), r.ntiles, fold_lane_block(kClassBits[c]), R.h_tkey[c]);
+        r.groups = R.tkey[c] + tiles;
+        r.ngroups = (uint32_t)(R.h_tkey[c].size() - tiles);
         if (is_wide_class(c)) units += exp_units(c, 0, r.ntiles);
         e = hipMemcpyAsync(R.desc[c], R.h_desc[c].data(), R.h_desc[c].size() * sizeof(ChunkDesc),
                            hipMemcpyHostToDevice, sv->stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(R.tkey[c], R.h_tkey[c].data(), tiles * sizeof(uint32_t), hipMemcpyHostToDevice,
+            e = hipMemcpyAsync(R.tkey[c], R.h_tkey[c].data(), R.h_tkey[c].size() * sizeof(uint32_t), hipMemcpyHostToDevice,
                                sv->stream);
         if (e != hipSuccess) return (int)e;
     }
