@@ -201,8 +201,9 @@ int pmk_decrypt_blinded_plan(pmk_plan *plan, const uint8_t *d_ct_star, const uin
  * it.  Encryption of the 3072- and 4096-bit classes is ONE persistent
  * work-queue launch whose waves take units (a quarter tile each) from a
  * device counter, 4096-bit units first; every other exponentiation is its
- * class's persistent kernel; for the CRT halves the two classes with the most
- * work get streams of their own and the others follow one another on a third.  The whole sequence (packing, exponentiation, CRT recombination,
+ * class's own launch; for the CRT halves the two classes with the most work
+ * get streams of their own, the larger first on `stream`, and the others follow
+ * one another on a third.  The whole sequence (packing, exponentiation, CRT recombination,
  * unpacking) is captured once into a HIP graph per (input, output) buffer pair
  * and replayed on `stream`; a new buffer pair or window setting recaptures it.
  * Results are byte-identical to pmk_encrypt_plan / pmk_decrypt_plan.  With
@@ -215,7 +216,7 @@ int pmk_encrypt_batch(pmk_plan *plan, const uint8_t *d_msg, uint8_t *d_ct, void 
 int pmk_decrypt_batch(pmk_plan *plan, const uint8_t *d_ct, uint8_t *d_msg, void *stream);
 
 /*
- * Tuning: the window width of the fixed-window CRT exponentiation (2..6) of
+ * Tuning: the window width of the sliding-window CRT exponentiation (2..6) of
  * the size class holding `bits`-bit moduli.  Changing it never changes
  * results, only speed; plans already made pick it up (graphs are recaptured).
  * pmk_get_window returns the width or a negative status.
@@ -226,26 +227,26 @@ int pmk_get_window(const pmk_ctx *ctx, uint32_t bits);
 /*
  * Tuning: lanes per number of the CRT exponentiations (the parallel loops of
  * Algorithm 1 over the chunks; plain and blinded decryption alike) of the size
- * class holding `bits`-bit moduli,
- * where a launch would leave SIMDs idle (L lanes per number shorten each
- * wave's chain about L times, for more instructions).  A class whose CRT halves run one lane per
- * number (128- to 4096-bit keys) runs
- *   - a launch under one round of resident waves with `fill_lanes` lanes per
- *     number, or the largest smaller power of two for which every lane-group
- *     wave still has a SIMD of its own (units of 64 numbers modulo one prime
- *     times L at most 4 per compute unit), else one lane, and
- *   - the partial round after full ones as a launch of its own (its waves
- *     then spread over the SIMDs) with `tail_lanes` lanes per number, or the
- *     largest smaller power of two whose waves fit one round,
- * each 1, 2 or 4: L lanes per number give L times the waves, each with a
- * shorter chain per Montgomery product, for about twice the instructions per
- * number.  The 6144/8192-bit classes run 4 lanes per number; their
- * `fill_lanes` may be 8 (a launch whose 8-lane waves each get a SIMD of their
- * own then runs with 8) and their `tail_lanes` must be 4; the one-lane classes
- * take 1, 2 or 4, and `fill_lanes` 8 at 2048, 3072 and 4096 bits (PMK_EUNSUPPORTED
- * for other supported counts, PMK_EINVAL for counts other than 1, 2, 4, 8).  Results never change; graphs are
- * recaptured; PMK_EBUSY while a server runs.  pmk_get_lanes fills the current
- * values.
+ * class holding `bits`-bit moduli, where a launch would leave SIMDs idle (more
+ * lanes per number shorten each wave's chain, for more instructions).
+ *   - 128- to 512-bit keys run one lane per number; a launch under one round of
+ *     resident waves runs with `fill_lanes` lanes per number, or the largest
+ *     smaller power of two for which every lane-group wave still has a SIMD of
+ *     its own (units of 64 numbers modulo one prime times L at most 4 per
+ *     compute unit); the partial round after full ones runs as a launch of its
+ *     own with `tail_lanes` lanes per number, or the largest smaller power of two
+ *     whose waves fit one round.
+ *   - 1024- to 4096-bit keys run one lane per number with the reduction on the
+ *     matrix cores; with `fill_lanes` above 1 a launch of few numbers spreads each
+ *     over a block of up to 4 waves instead (blinded decryption: 8 or 4 lanes at
+ *     2048 to 4096 bits), and so does a partial round where a SIMD holds one wave.
+ *   - 6144- and 8192-bit keys run 4 lanes per number with `fill_lanes` 4, and
+ *     each number over a block of 7 or 8 waves with 8 (blinded decryption: 8
+ *     lanes in a small launch); their `tail_lanes` must be 4.
+ * The one-lane classes take 1, 2 or 4, and `fill_lanes` 8 at 2048, 3072 and 4096
+ * bits (PMK_EUNSUPPORTED for other supported counts, PMK_EINVAL for counts other
+ * than 1, 2, 4, 8).  Results never change; graphs are recaptured; PMK_EBUSY while
+ * a server runs.  pmk_get_lanes fills the current values.
  */
 int pmk_set_lanes(pmk_ctx *ctx, uint32_t bits, int fill_lanes, int tail_lanes);
 int pmk_get_lanes(const pmk_ctx *ctx, uint32_t bits, int *fill_lanes, int *tail_lanes);
@@ -270,9 +271,10 @@ int pmk_set_grid_limit(pmk_ctx *ctx, uint32_t waves);
  * resident waves at three window widths ({4,5,6} for 1024-bit classes and up,
  * {3,4,5} below), keeping the fastest (pmk_set_window); then, for the classes
  * with one lane per number, a launch of a quarter of the compute units' worth
- * of job tiles and one of one and a third rounds at 1, 2 and 4 lanes per
- * number (fill also 8 at 2048-4096 bits), keeping the fastest fill and
- * tail forms, and for the 6144/8192-bit classes the first of these at 4 and 8
+ * of job tiles (and, up to 512 bits, one of one and a third rounds) at 1, 2 and
+ * 4 lanes per number -- from 1024 bits on at one and at the class's largest
+ * count --, keeping the fastest fill and tail forms, and for the
+ * 6144/8192-bit classes the first of these at 4 and 8
  * lanes (pmk_set_lanes); a form with more lanes is kept only if it wins by
  * 1 %.  cache_path (may be NULL): a
  * text file -- a signature line (GPU architecture, compute units, HIP runtime

@@ -262,6 +262,12 @@ __device__ __forceinline__ void fold_mul(uint32_t (&r)[NL], const uint32_t (&a)[
         constexpr int lo = Order::lo(k), n = Order::mads(c);
         if constexpr (c == NL + 1) acc = 0;
         auto products = [&](int from, int to) {
+            // at 56 limbs a stretch can start with a reload from scratch: waited for before
+            // the alignment
+            if constexpr (NL == 56) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (from < to) asm volatile("" ::"v"(a[lo + from]), "v"(b[k - lo - from]));
+            }
             fold_align();
 #pragma unroll
             for (int i = lo + from; i < lo + to; ++i) acc += (uint64_t)a[i] * b[k - i];

@@ -148,13 +148,140 @@ PMK_DEV void reduce_two(uint32_t (&a)[NL], uint32_t (&b)[NL], uint32_t (&c)[NL],
     }
 }
 
+// Blinded decryption, job (tile, prime h): (c*)^d c_R^(m-1-d) mod m in one
+// chain, the interleaved sliding windows of halves_joint_unit on fold products.
+// c* from r.x32, c_R from r.fin32 (whether m divides c_R: blind_check_kernel).
+template <int CB>
+PMK_DEV void halves_fold_joint_unit(const ClassRun &r, uint32_t tile, int h, uint32_t *tbl, FoldLds f, uint32_t *lds) {
+    constexpr Geom G = make_geom(CB);
+    constexpr int NL = fold_lane(CB).nl, LB = fold_lane(CB).lb, S = G.S, SH = G.SH;
+    const int win = r.win, TH = 1 << (win - 1);  // T1 = entries [0, TH), T2 = [TH, 2 TH)
+    const int lane = threadIdx.x & 63;
+    const uint32_t *hr = r.keys + (size_t)uni(r.tile_key[tile]) * G.stride + G.off_half[0] + h * G.h_size;
+    const uint32_t *d1 = hr + G.h_d, *d2 = hr + G.h_d2;
+    uint32_t one = 1, k16 = 1u << 16;
+    asm volatile("" : "+s"(one), "+s"(k16));
+
+    uint32_t acc[NL], b[NL], x[NL];
+    fold_words<NL, LB, S>(acc, fresh_v(r.x32 + (size_t)tile * S * kTile + lane), f, lane);
+    store_row4(tbl, 0, lane, acc);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) b[j] = acc[j];
+    __builtin_amdgcn_s_waitcnt(0);
+    // phases: 2 x^2, 3 odd powers (of c*, k = 0, then of c_R, k = 1), 5 the chain
+    int phase = 2, k = 0, e = 1, sq = 0, nsq = 0, pos = 0;
+    uint32_t pend = 0;
+    WinStep s1 = WinStep::make(0, 0u, false, -1), s2 = s1;
+    ExpWords nx1{0u, 0u, 0u}, nx2{0u, 0u, 0u};
+    for (;;) {
+        if (phase == 5) {
+            const uint32_t ent = (pend & 1u) ? s1.idx() : TH + s2.idx();  // the event's first product
+            if (sq < nsq) {
+                if (fold_lane_prefetch(CB) && sq == 0 && pend) prefetch_row4<NL>(lds, tbl, ent, lane);
+#pragma unroll
+                for (int j = 0; j < NL; ++j) b[j] = acc[j] << 1;
+                fold_mul<NL, LB, true>(x, acc, b, f, lane, one, k16);
+#pragma unroll
+                for (int j = 0; j < NL; ++j) acc[j] = x[j];
+                ++sq;
+                continue;
+            }
+            if (!pend) break;
+            if (fold_lane_prefetch(CB) && sq == nsq) take_row4(b, lds, lane);
+            else load_row4(b, tbl, sq == nsq ? ent : TH + s2.idx(), lane);  // windows of both exponents end here: T2 second
+            __builtin_amdgcn_s_waitcnt(0);
+            ++sq;
+        }
+        fold_mul<NL, LB, false>(x, acc, b, f, lane, one, k16);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) acc[j] = x[j];
+        const int base = k * TH;
+        if (phase == 2) {
+#pragma unroll
+            for (int j = 0; j < NL; ++j) b[j] = acc[j];  // x^2, the step between odd powers
+            load_row4(acc, tbl, base, lane);
+            phase = 3;
+            e = 1;
+            __builtin_amdgcn_s_waitcnt(0);
+            continue;
+        }
+        if (phase == 3) {
+            store_row4(tbl, base + e, lane, acc);
+            ++e;
+            __builtin_amdgcn_s_waitcnt(0);
+            if (e < TH) continue;
+            if (k == 0) {  // c_R next
+                k = 1;
+                fold_words<NL, LB, S>(acc, fresh_v(r.fin32 + (size_t)tile * S * kTile + lane), f, lane);
+                store_row4(tbl, TH, lane, acc);
+#pragma unroll
+                for (int j = 0; j < NL; ++j) b[j] = acc[j];
+                phase = 2;
+                __builtin_amdgcn_s_waitcnt(0);
+                continue;
+            }
+            // tables complete: the chain starts from 1 above the higher top bit
+#pragma unroll
+            for (int j = 0; j < NL; ++j) acc[j] = j == 0 ? 1u : 0u;
+            const int t1 = exp_top_bit(d1, SH), t2 = exp_top_bit(d2, SH);
+            if (t1 >= 0) s1 = win_first(nx1, d1, SH, t1, win);
+            if (t2 >= 0) s2 = win_first(nx2, d2, SH, t2, win);
+            pos = (t1 > t2 ? t1 : t2) + 1;
+            phase = 5;
+        } else if (sq == nsq + 1 && pend == 3u) {
+            continue;  // the T1 product is done, the T2 product of the same event follows
+        } else {  // the event's products are done
+            if (pend & 1u) win_advance(s1, nx1, d1, SH, win);
+            if (pend & 2u) win_advance(s2, nx2, d2, SH, win);
+        }
+        // next event: the higher window end still pending (window [l, ...], l = next + 1)
+        const int l1 = s1.mul() ? s1.next() + 1 : -1, l2 = s2.mul() ? s2.next() + 1 : -1;
+        const int ev = l1 > l2 ? l1 : l2;
+        pend = ev < 0 ? 0u : (l1 == ev ? 1u : 0u) | (l2 == ev ? 2u : 0u);
+        nsq = pos - (ev < 0 ? 0 : ev);  // no window left: square down to bit 0
+        pos = ev < 0 ? 0 : ev;
+        sq = 0;
+    }
+    uint32_t *dst = r.half + ((size_t)(2 * tile + h) * half_stride(CB)) * kTile + lane;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) dst[(size_t)j * kTile] = acc[j];
+}
+
+// Sets bit 1 of r.err where a prime divides a chunk's c_R (r.fin32): c_R mod m as
+// fold_finish_unit computes it, 0 or m.  Block jt = job tile.
+template <int CB>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(make_geom(CB).nlh > 40 ? 1 : 2))) void blind_check_kernel(
+    ClassRun r) {
+    constexpr Geom G = make_geom(CB);
+    constexpr int NL = G.nlh, LB = G.lbh, S = G.S;
+    const uint32_t jt = blockIdx.x, tile = jt >> 1;
+    const int lane = threadIdx.x;
+    const uint32_t *hr = r.keys + (size_t)uni(r.tile_key[tile]) * G.stride + G.off_half[0] + (jt & 1) * G.h_size;
+    const uint32_t *w = r.fin32 + (size_t)tile * S * kTile + lane;
+    uint32_t n[NL], a[NL], b[NL], c[NL];
+    load_uniform(n, hr + G.h_m);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+        a[j] = radix_limb_mem<S, LB>(w, kTile, j);
+        c[j] = radix_limb_mem<S, LB>(w, kTile, NL + j);
+    }
+    reduce_two<NL, LB>(a, b, c, n, hr, G.h_rr, G.h_rrr, uni(hr[G.h_m0]));
+    uint32_t z = 0, q = 0;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+        z |= a[j];
+        q |= a[j] ^ n[j];
+    }
+    if ((z == 0 || q == 0) && r.desc[(size_t)tile * kTile + lane].msg_len) atomicOr(r.err, 2u);
+}
+
 // Units [u_begin, u_end): u = 2 group + h, one wave per tile of the group (fewer
 // waves than tiles: each takes several).  split: units are single tiles instead,
 // u = 2 (per group + tile of the group) + h, for blocks of one wave (launches
 // that leave SIMDs idle: one-wave blocks spread over the four SIMDs of a compute
 // unit, two-wave blocks were measured two deep on half of them, 5.0 against
 // 3.5 us per 2048-bit square with a wave per SIMD).
-template <int CB>
+template <int CB, bool JOINT = false>
 PMK_DEV void halves_fold_block(const ClassRun &r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end, bool split,
                                uint32_t *table, uint32_t *entry) {
     constexpr uint32_t per = fold_lane_block(CB);
@@ -174,7 +301,8 @@ PMK_DEV void halves_fold_block(const ClassRun &r, uint64_t slot_words, uint32_t 
         if (t0 >= tiles && u + gridDim.x >= u_end) return;
         for (int t = t0; t < (split ? t0 + 1 : tiles); t += nw) {
             uint32_t *ent = entry + (fold_lane_prefetch(CB) ? wave * FoldHalves<CB>::ROW4 : 0);
-            halves_fold_unit<CB>(r, first + t, h, tbl, FoldLds{(const uint8_t *)table}, ent);
+            if constexpr (JOINT) halves_fold_joint_unit<CB>(r, first + t, h, tbl, FoldLds{(const uint8_t *)table}, ent);
+            else halves_fold_unit<CB>(r, first + t, h, tbl, FoldLds{(const uint8_t *)table}, ent);
         }
     }
 }

@@ -4,16 +4,18 @@
 //             (Sec. 3.1: the message as a vector of chunk integers)
 //   encrypt   c = m^e mod N, left-to-right binary exponentiation
 //             (Sec. 1.1 step 2; Algorithm 2 in its left-to-right form)
-//   halves    m_p = c^dp mod p and m_q = c^dq mod q, fixed-window
-//             exponentiation (Sec. 2.1, equation CRT-RSA; Algorithm 2 with
-//             w-bit digits instead of bits)
+//   halves    m_p = c^dp mod p and m_q = c^dq mod q, sliding windows
+//             (Sec. 2.1, equation CRT-RSA; Algorithm 2 with windows of up to
+//             w bits instead of bits)
 //   garner    h = qinv (m_p - m_q) mod p, m = m_q + h q (Sec. 2.1)
 //   unpack    32-bit limbs -> big-endian bytes of each block
 //
-// Every CRT half (up to 2048 bits) and every full-size number up to 2048 bits
-// is one lane's work (64 bignums per wavefront, Montgomery products in
-// mont.hpp); full-size 3072- and 4096-bit numbers (encryption) are spread over
-// 4 lanes (mont_lanes.hpp).  A tile holds 64 chunks under one key, so the
+// The CRT halves of 1024- to 8192-bit keys reduce on the matrix cores
+// (halves_fold.hpp: one lane per number; halves_group.hpp: a number over a
+// block).  Smaller halves and every full-size number up to 2048 bits are one
+// lane's work (64 bignums per wavefront, Montgomery products in mont.hpp);
+// full-size 3072- and 4096-bit numbers (encryption) are spread over 4 lanes
+// (mont_lanes.hpp).  A tile holds 64 chunks under one key, so the
 // modulus and exponent are wave-uniform.
 // The exponentiation kernels are persistent: each 64-thread block owns a
 // scratch slot for its window table and walks tiles blockIdx.x, +gridDim.x, ...
@@ -385,13 +387,6 @@ PMK_DEV void encrypt_unit(const ClassRun r, uint32_t tile, uint32_t *tbl) {
 // x~ = MM(c_lo, R^2) + MM(c_hi, R^3) = c R mod p (below 4p), with
 // c = c_hi 2^(LB NL) + c_lo.  Then sliding windows of at most r.win bits over
 // a table of the odd powers x~^(2j+1), and a last product by 1.
-PMK_DEV uint32_t digit_of(const uint32_t *d, int SH, int k, int w) {
-    const int pos = k * w;
-    const int wd = pos >> 5, sh = pos & 31;
-    const uint32_t lo = d[wd];
-    const uint32_t hi = (wd + 1) < SH ? d[wd + 1] : 0u;
-    return (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & ((1u << w) - 1u);
-}
 
 // Bits of a wave-uniform exponent of SH words (scalar registers and branches).
 PMK_DEV uint32_t exp_bit(const uint32_t *d, int k) { return (uni(d[k >> 5]) >> (k & 31)) & 1u; }
@@ -491,44 +486,22 @@ PMK_DEV void halves_unit(const ClassRun r, uint32_t jt, uint32_t *tbl, uint32_t 
     const uint32_t *one_h = hr + G.h_one;
 
     uint32_t acc[NL], b[NL];
-    if constexpr (S <= 64) {
-        uint32_t w[S];
+    uint32_t w[S];
 #pragma unroll
-        for (int k = 0; k < S; ++k) w[k] = r.x32[((size_t)tile * S + k) * kTile + lane];
-        if (h == 0 && r.desc[(size_t)tile * kTile + lane].msg_len) {
-            // C must lie in Z_N: compare with N, most significant word first
-            const uint32_t *n32 = kr + G.off_n32;
-            int cmp = 0;
+    for (int k = 0; k < S; ++k) w[k] = r.x32[((size_t)tile * S + k) * kTile + lane];
+    if (h == 0 && r.desc[(size_t)tile * kTile + lane].msg_len) {
+        // C must lie in Z_N: compare with N, most significant word first
+        const uint32_t *n32 = kr + G.off_n32;
+        int cmp = 0;
 #pragma unroll
-            for (int k = S - 1; k >= 0; --k) cmp = cmp ? cmp : (w[k] > n32[k]) - (w[k] < n32[k]);
-            if (cmp >= 0) atomicOr(r.err, 1u);
-        }
-#pragma unroll
-        for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j + NL);
-        store_row4(tbl, 0, lane, acc);  // c_hi, parked in entry 0 until it is used
-#pragma unroll
-        for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j);
-    } else {
-        // 3072/4096 bits: the ciphertext words are read from the tile in memory
-        // (staging up to 128 words in registers would spill)
-        const uint32_t *w = fresh_v(r.x32 + (size_t)tile * S * kTile + lane);
-        if (h == 0 && r.desc[(size_t)tile * kTile + lane].msg_len) {
-            // C must lie in Z_N: compare with N, most significant word first
-            const uint32_t *n32 = kr + G.off_n32;
-            int cmp = 0;
-#pragma unroll 1
-            for (int k = S - 1; k >= 0 && cmp == 0; --k) {
-                const uint32_t x = w[(size_t)k * kTile], y = n32[k];
-                cmp = (x > y) - (x < y);
-            }
-            if (cmp >= 0) atomicOr(r.err, 1u);
-        }
-#pragma unroll
-        for (int j = 0; j < NL; ++j) acc[j] = radix_limb_mem<S, LB>(w, kTile, j + NL);
-        store_row4(tbl, 0, lane, acc);  // c_hi, parked in entry 0 until it is used
-#pragma unroll
-        for (int j = 0; j < NL; ++j) acc[j] = radix_limb_mem<S, LB>(w, kTile, j);
+        for (int k = S - 1; k >= 0; --k) cmp = cmp ? cmp : (w[k] > n32[k]) - (w[k] < n32[k]);
+        if (cmp >= 0) atomicOr(r.err, 1u);
     }
+#pragma unroll
+    for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j + NL);
+    store_row4(tbl, 0, lane, acc);  // c_hi, parked in entry 0 until it is used
+#pragma unroll
+    for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j);
     load_limbs(b, hr + G.h_rr);
 
     const int TH = 1 << (win - 1);  // odd powers x~, x~^3, ..., x~^(2 TH - 1)
@@ -1288,20 +1261,28 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kEncWaves<CB
 }
 
 // blinded decryption in one pass (every class: one lane per number up to 4096
-// bits, lane groups above; the chain uses sliding windows whatever the class's
-// plain decryption uses); two waves per SIMD: the second table's state does not
-// fit the three-wave budget
+// bits, in the fold form from 1024 bits on, lane groups above); units as in
+// halves_kernel
 template <int CB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void halves_joint_kernel(
-    ClassRun r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end) {
+constexpr int kJointBlock = fold_lane(CB).nl ? 64 * fold_lane_block(CB) : 64;
+template <int CB>
+__global__ __launch_bounds__(kJointBlock<CB>)
+    __attribute__((amdgpu_waves_per_eu(fold_lane(CB).nl ? fold_joint_waves(CB) : 2))) void halves_joint_kernel(
+        ClassRun r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end, bool split) {
     code_align<code_id(kCodeJoint, CB, 0)>();
-    uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
-    __shared__ uint32_t lds[lds_words_dec<CB>()];
-    for (uint32_t u = u_begin + blockIdx.x; u < u_end; u += gridDim.x) {
-        if constexpr (lanes_half(CB) > 1)
-            halves_lanes_joint_unit<CB>(r, u, tbl, lds);
-        else
-            halves_joint_unit<CB>(r, u, tbl, lds);
+    if constexpr (fold_lane(CB).nl != 0) {
+        __shared__ __align__(16) uint32_t table[FoldHalves<CB>::WORDS];
+        __shared__ __align__(16) uint32_t entry[fold_lane_prefetch(CB) ? fold_lane_block(CB) * FoldHalves<CB>::ROW4 : 4];
+        halves_fold_block<CB, true>(r, slot_words, u_begin, u_end, split, table, entry);
+    } else {
+        uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
+        __shared__ uint32_t lds[lds_words_dec<CB>()];
+        for (uint32_t u = u_begin + blockIdx.x; u < u_end; u += gridDim.x) {
+            if constexpr (lanes_half(CB) > 1)
+                halves_lanes_joint_unit<CB>(r, u, tbl, lds);
+            else
+                halves_joint_unit<CB>(r, u, tbl, lds);
+        }
     }
 }
 

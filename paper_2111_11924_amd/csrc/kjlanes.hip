@@ -1,8 +1,9 @@
 // Blinded decryption (one pass per prime, Sec. 3.1) in lane groups
 // (halves_lanes_joint_kernel) for the part of a launch that leaves SIMDs idle:
-// the one-lane classes (128- to 4096-bit keys) with 2 or 4 lanes per number as
-// lanes_for_launch decides, the lane-group classes (6144/8192) with 8 instead
-// of 4 as wide_fill decides.  A translation unit of its own, so the other
+// 128- to 512-bit keys with 2 or 4 lanes per number and small launches of 2048- (8
+// lanes) and 3072- to 4096-bit keys (4 or 8), where the fold form is not faster, as
+// lanes_for_launch decides; the lane-group classes (6144/8192) with 8 instead of 4
+// as wide_fill decides.  A translation unit of its own, so the other
 // objects stay as they are and the classes compile in parallel with them.
 #include "kernels_impl.hpp"
 
@@ -42,8 +43,10 @@ int launch_class(const ClassRun &r, uint32_t jt_begin, uint32_t jt_end, hipStrea
 template <int CB>
 int launch_L(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, hipStream_t s) {
     if constexpr (lanes_half(CB) == 1) {
-        if (L == 2) return launch_class<CB, 2>(r, jt_begin, jt_end, s);
-        if (L == 4) return launch_class<CB, 4>(r, jt_begin, jt_end, s);
+        if constexpr (CB <= 512)
+            if (L == 2) return launch_class<CB, 2>(r, jt_begin, jt_end, s);
+        if constexpr (CB <= 512 || CB >= 3072)
+            if (L == 4) return launch_class<CB, 4>(r, jt_begin, jt_end, s);
         if constexpr (eight_lanes(CB))
             if (L == 8) return launch_class<CB, 8>(r, jt_begin, jt_end, s);
     } else {
@@ -62,15 +65,9 @@ uint32_t joint_lanes_resident(int cls, int L) {
         case 1 * 16 + 4: return resident_of<256, 4>();
         case 2 * 16 + 2: return resident_of<512, 2>();
         case 2 * 16 + 4: return resident_of<512, 4>();
-        case 3 * 16 + 2: return resident_of<1024, 2>();
-        case 3 * 16 + 4: return resident_of<1024, 4>();
-        case 4 * 16 + 2: return resident_of<2048, 2>();
-        case 4 * 16 + 4: return resident_of<2048, 4>();
         case 4 * 16 + 8: return resident_of<2048, 8>();
-        case 5 * 16 + 2: return resident_of<3072, 2>();
         case 5 * 16 + 4: return resident_of<3072, 4>();
         case 5 * 16 + 8: return resident_of<3072, 8>();
-        case 6 * 16 + 2: return resident_of<4096, 2>();
         case 6 * 16 + 4: return resident_of<4096, 4>();
         case 6 * 16 + 8: return resident_of<4096, 8>();
         case 7 * 16 + 2 * lanes_half(6144): return resident_of<6144, 2 * lanes_half(6144)>();
@@ -86,7 +83,6 @@ int launch_joint_lanes(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_
         case 0: return launch_L<128>(r, L, jt_begin, jt_end, s);
         case 1: return launch_L<256>(r, L, jt_begin, jt_end, s);
         case 2: return launch_L<512>(r, L, jt_begin, jt_end, s);
-        case 3: return launch_L<1024>(r, L, jt_begin, jt_end, s);
         case 4: return launch_L<2048>(r, L, jt_begin, jt_end, s);
         case 5: return launch_L<3072>(r, L, jt_begin, jt_end, s);
         case 6: return launch_L<4096>(r, L, jt_begin, jt_end, s);

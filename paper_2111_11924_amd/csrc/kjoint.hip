@@ -12,7 +12,69 @@ namespace pmk {
 namespace {
 
 template <int CB>
+int launch_joint_lane_class(const ClassRun &r, hipStream_t s);
+
+// Fold form: blocks as for the plain halves (25 MiB under 2048-bit keys: 27.5 ms with
+// Montgomery products, 22.1 ms here).  A small launch runs over lane groups instead
+// while each of their waves has a SIMD of its own: eight lanes take 4.6 / 10.0 / 20.5
+// ms at 2048 / 3072 / 4096 bits against 5.1 / 17.4 / 40.6 in one lane; four lanes pay
+// at 3072 (12.1 ms) and 4096 bits, no longer at 2048 (5.3 ms), two at none (4096: 45 ms).
+template <int CB>
+int launch_joint_fold(const ClassRun &r, hipStream_t s) {
+    constexpr uint32_t per = fold_lane_block(CB);
+    static const uint32_t occ = [] {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)halves_joint_kernel<CB>, kJointBlock<CB>, 0) !=
+                hipSuccess ||
+            nb < 1)
+            nb = 1;
+        return (uint32_t)nb;
+    }();
+    const uint32_t cus = (uint32_t)device_cus();
+    uint32_t waves = per * occ * cus;
+    if (r.grid_cap && r.grid_cap < waves) waves = r.grid_cap;
+    if (eight_lanes(CB) && 2 * r.ntiles < waves && r.slots_dec >= 4 * r.ntiles) {
+        uint32_t lane_units = 0;
+        const int L = lanes_for_launch(r, 2 * r.ntiles, waves, 4u * cus, joint_lanes_resident, &lane_units);
+        if (L > 1) return launch_joint_lanes(r, L, 0, 2 * r.ntiles, s);
+    }
+    if (r.slots_dec < waves) waves = r.slots_dec;
+    const uint32_t nw = waves < r.group_tiles ? waves : r.group_tiles;
+    const uint32_t round = waves / (2 * per) ? waves / (2 * per) : 1;  // groups
+    uint32_t full = r.ngroups;
+    if (per == 2 && waves >= 2) {
+        const uint32_t rest = r.ngroups <= round ? r.ngroups : r.ngroups % round;
+        if (4 * rest <= 4u * cus) full -= rest;
+    }
+    const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
+    int e = 0;
+    if (full) {
+        hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * full, waves / nw, 0)), dim3(64 * nw), 0, s, r,
+                           slot, 0u, 2 * full, false);
+        e = (int)hipGetLastError();
+    }
+    if (!e && full < r.ngroups) {
+        hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * per * (r.ngroups - full), waves, 0)), dim3(64), 0,
+                           s, r, slot, 2 * per * full, 2 * per * r.ngroups, true);
+        e = (int)hipGetLastError();
+    }
+    if (e) return e;
+    hipLaunchKernelGGL(blind_check_kernel<CB>, dim3(2 * r.ntiles), dim3(64), 0, s, r);
+    e = (int)hipGetLastError();
+    if (e) return e;
+    hipLaunchKernelGGL((fold_finish_kernel<CB, fold_lane(CB).nl, fold_lane(CB).lb>), dim3(2 * r.ntiles), dim3(64), 0, s, r,
+                       0u, 0u);
+    return (int)hipGetLastError();
+}
+
+template <int CB>
 int launch_joint_class(const ClassRun &r, hipStream_t s) {
+    if constexpr (fold_lane(CB).nl != 0) return launch_joint_fold<CB>(r, s);
+    else return launch_joint_lane_class<CB>(r, s);
+}
+
+template <int CB>
+int launch_joint_lane_class(const ClassRun &r, hipStream_t s) {
     // resident blocks on this device; never more than the r.slots_dec table slots
     // (those of the CRT-halves kernel, which is at least as occupied and capped by
     // the same unit count)
@@ -49,14 +111,14 @@ int launch_joint_class(const ClassRun &r, hipStream_t s) {
     const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
     if (main_end) {
         hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(main_end, grid, 0)), dim3(64), 0, s, r, slot,
-                           0u, main_end);
+                           0u, main_end, false);
         const int e = (int)hipGetLastError();
         if (e) return e;
     }
     if (main_end == units) return 0;
     if (L == 1) {  // the partial round, one lane per number, in a launch of its own
         hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(units - main_end, grid, 0)), dim3(64), 0, s,
-                           r, slot, main_end, units);
+                           r, slot, main_end, units, false);
         return (int)hipGetLastError();
     }
     return launch_joint_lanes(r, L, main_end / lanes_half(CB), 2 * r.ntiles, s);

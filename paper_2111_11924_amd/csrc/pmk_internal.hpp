@@ -41,7 +41,7 @@ PMK_HD constexpr uint32_t persistent_grid(uint32_t units, uint32_t slots, uint32
     return cap && cap < g ? cap : g;
 }
 
-// Default window width of the fixed-window exponentiation of the CRT halves
+// Default width of the sliding windows of the CRT halves
 // (the autotuner may pick another one up to kMaxWin).
 PMK_HD constexpr int window_for(int bits) { return bits <= 256 ? 3 : (bits <= 512 ? 4 : 5); }
 
@@ -170,6 +170,9 @@ PMK_HD constexpr FoldForm fold_lane(int bits) {
 // product (where the table leaves room)
 PMK_HD constexpr int fold_lane_block(int bits) { return bits >= 3072 ? 4 : 2; }
 PMK_HD constexpr int fold_lane_waves(int bits) { return bits >= 4096 ? 1 : (bits >= 2048 ? 2 : 3); }
+// the blinded form: its second window spills at three waves per SIMD (25 MB under
+// 1024-bit keys: 9.8 / 9.2 ms with two)
+PMK_HD constexpr int fold_joint_waves(int bits) { return fold_lane_waves(bits) < 2 ? 1 : 2; }
 PMK_HD constexpr bool fold_lane_prefetch(int bits) { return bits <= 2048; }
 // a number spread over a block (small launches; the classes above); nl a
 // multiple of 4, LB = 28: limbs there carry up to twice 2^lb
@@ -259,12 +262,8 @@ struct ClassRun {
 };
 
 constexpr int kMaxWin = 6;
-// default lanes per number of a one-lane class's CRT halves in a launch that
-// fills at most half a round, and in a short last round after full ones
-// (measured: 4 lanes cut a 1 MiB 2048-bit decryption by a fifth; a 2-lane
-// last round of the 100 MiB one is about even)
-// One-lane classes whose CRT halves also run in groups of 8 lanes (2048- to
-// 4096-bit keys, the classes whose record holds the nla8-limb constants), for
+// One-lane classes whose blinded CRT halves also run in groups of 8 lanes (2048-
+// to 4096-bit keys, the classes whose record holds the nla8-limb constants), for
 // small launches.
 PMK_HD constexpr bool eight_lanes(int bits) { return lanes_half(bits) == 1 && bits >= 2048; }
 
@@ -276,7 +275,9 @@ PMK_HD constexpr int lane_rr(const Geom &g, int L) { return L == 8 ? g.h_rra8 : 
 PMK_HD constexpr int lane_rrr(const Geom &g, int L) { return L == 8 ? g.h_rrra8 : g.h_rrra; }
 // Lanes-per-number settings a class takes: a one-lane class 1, 2 or 4 for
 // both forms, and 8 for small launches where eight_lanes; a lane-group class
-// its own count L0, or 2 L0 for small launches, and L0 for the tail form.
+// its own count L0, or 2 L0 for small launches, and L0 for the tail form.  From
+// 1024 bits on a fill count above lanes_half lets a small plain launch run with
+// each number over a block (group_launch).
 PMK_HD constexpr bool lanes_valid(int bits, int fill, int tail) {
     return lanes_half(bits) == 1
                ? ((fill == 1 || fill == 2 || fill == 4 || (fill == 8 && eight_lanes(bits))) &&
@@ -339,14 +340,13 @@ uint32_t tile_groups(const Vec &tile_key, uint32_t ntiles, int per, Vec &out) {
 // words per slot
 int launch_decrypt_joint(const ClassRun &r, void *stream);
 // CRT halves of job tiles [jt_begin, jt_end) in lane groups of L lanes per
-// number: a one-lane class (128..4096 bits) with L = 2 or 4, a lane-group class
-// (6144/8192 bits) with twice its own L (klanes.hip)
+// number: the 128- to 512-bit classes with L = 2 or 4 (klanes.hip)
 int launch_halves_lanes(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, void *stream);
 // resident waves of that lane-group kernel on the current device (0: no such kernel)
 uint32_t lanes_resident(int cls, int L);
 // Blinded decryption (one pass per prime) of job tiles [jt_begin, jt_end) in
-// lane groups of L lanes (a one-lane class: 2 or 4; a lane-group class: twice
-// its own), and that kernel's resident waves (kjlanes.hip)
+// lane groups of L lanes (those that joint_lanes_resident knows; a lane-group
+// class: twice its own), and that kernel's resident waves, 0 without one (kjlanes.hip)
 int launch_joint_lanes(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, void *stream);
 uint32_t joint_lanes_resident(int cls, int L);
 

@@ -125,3 +125,37 @@ def test_extreme_blocks(torch, ctx, bits, lanes, win):
     with ThreadPoolExecutor(8) as ex:
         want = list(ex.map(lambda v: oracle.rsa_int(table, 0, "crt", v), vals))
     assert [int.from_bytes(got[i * kb : (i + 1) * kb], "big") for i in range(len(vals))] == want
+
+
+@pytest.mark.parametrize("cap", [0, 3])
+@pytest.mark.parametrize("bits,win", [(1024, 2), (1536, 4), (2048, 5), (3072, 5), (4096, 5)])
+def test_blinded_tile_and_group_edges(torch, ctx, bits, win, cap):
+    """Both exponents in one chain per prime, at the edges of tiles and groups; a
+    blinding factor that one of the primes divides is flagged and harms no other chunk."""
+    counts = [1, 63, 64, 65, 129, 257] if not cap else [129, 1]
+    keys = keys_of(bits, len(counts))
+    kb = bits // 8
+    km = np.repeat(np.arange(len(counts), dtype=np.uint32), counts)
+    msg = inputs.make_message(len(km) * (kb - 4) - 7, bits + 1)
+    ctx.load_keys(keys)
+    old = ctx.lanes(bits), ctx.window(bits)
+    ctx.set_lanes(bits, 1, old[0][1])
+    ctx.set_window(bits, win)
+    ctx.set_grid_limit(cap)
+    try:
+        plan = ctx.plan(km, len(msg))
+        for bad in (None, keys[0].p, keys[0].q * 2):
+            rblk = inputs.make_blinding(keys, km, bits)
+            if bad:
+                rblk[:kb] = np.frombuffer(bad.to_bytes(kb, "big"), np.uint8)
+            cs, cr = plan.encrypt_blinded(torch.from_numpy(msg).cuda(), torch.from_numpy(rblk).cuda())
+            assert plan.check() == binding.PMK_OK
+            got = plan.decrypt_blinded(cs, cr)
+            assert plan.check() == (binding.PMK_EBLIND if bad else binding.PMK_OK)
+            skip = kb - 4 if bad else 0
+            np.testing.assert_array_equal(got[skip : len(msg)].cpu().numpy(), msg[skip:])
+        plan.close()
+    finally:
+        ctx.set_grid_limit(0)
+        ctx.set_window(bits, old[1])
+        ctx.set_lanes(bits, *old[0])
