@@ -307,6 +307,47 @@ PMK_DEV void halves_fold_block(const ClassRun &r, uint64_t slot_words, uint32_t 
     }
 }
 
+// The partial round after full ones, as blocks of two units (group, h): four waves,
+// one on each SIMD, which blocks of one or two waves do not ensure after the full
+// rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 3.7
+// ms here; 15 MB under 1024-bit keys 4.46 / 3.90 ms; from an idle chip blocks of one
+// wave are as even and 3 to 7 % faster).  table and entry hold two tables and four rows,
+// and fill LDS so that one block fewer fits a compute unit than the class has waves per SIMD.
+template <int CB>
+struct FoldQuad {
+    static constexpr int WORDS = 2 * FoldHalves<CB>::WORDS;
+    static constexpr int ROWS = 4 * FoldHalves<CB>::ROW4, FILL = (160 / fold_lane_waves(CB) + 1) * 256;  // words
+    static constexpr int ENTRY = WORDS + ROWS > FILL ? ROWS : FILL - WORDS;
+};
+template <int CB, bool JOINT = false>
+PMK_DEV void halves_fold_quad(const ClassRun &r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end, uint32_t *table,
+                              uint32_t *entry) {
+    const int wave = (int)uni(threadIdx.x / 64), team = wave >> 1;
+    const uint32_t u = u_begin + 2 * blockIdx.x + team;
+    table += team * FoldHalves<CB>::WORDS;
+    uint32_t grp = 0;
+    if (u < u_end) {
+        grp = uni(r.groups[u >> 1]);
+        const uint4 *src = (const uint4 *)(r.fold +
+                                           (size_t)(2 * uni(r.tile_key[grp & 0x3FFFFFFFu]) + (u & 1)) * fold_table(CB).size +
+                                           fold_table(CB).lane);
+        for (int i = threadIdx.x & 127; i < FoldHalves<CB>::WORDS / 4; i += 128) ((uint4 *)table)[i] = src[i];
+    }
+    __syncthreads();
+    if (u >= u_end || (uint32_t)(wave & 1) > grp >> 30) return;
+    const uint32_t tile = (grp & 0x3FFFFFFFu) + (wave & 1);
+    uint32_t *tbl = r.table + ((size_t)blockIdx.x * 4 + wave) * slot_words, *ent = entry + wave * FoldHalves<CB>::ROW4;
+    if constexpr (JOINT) halves_fold_joint_unit<CB>(r, tile, u & 1, tbl, FoldLds{(const uint8_t *)table}, ent);
+    else halves_fold_unit<CB>(r, tile, u & 1, tbl, FoldLds{(const uint8_t *)table}, ent);
+}
+template <int CB, bool JOINT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JOINT ? fold_joint_waves(CB) : fold_lane_waves(CB)))) void halves_quad_kernel(
+    ClassRun r, uint64_t slot_words, uint32_t u_begin, uint32_t u_end) {
+    __shared__ __align__(16) uint32_t table[FoldQuad<CB>::WORDS];
+    __shared__ __align__(16) uint32_t entry[FoldQuad<CB>::ENTRY];
+    halves_fold_quad<CB, JOINT>(r, slot_words, u_begin, u_end, table, entry);
+}
+
 // Canonical halves from fold results (nl limbs of lb bits, loose), in place.
 // One lane per number.
 template <int CB, int FNL, int FLB>

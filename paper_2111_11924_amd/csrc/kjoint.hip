@@ -42,9 +42,11 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     const uint32_t nw = waves < r.group_tiles ? waves : r.group_tiles;
     const uint32_t round = waves / (2 * per) ? waves / (2 * per) : 1;  // groups
     uint32_t full = r.ngroups;
+    bool quad = false;
     if (per == 2 && waves >= 2) {
         const uint32_t rest = r.ngroups <= round ? r.ngroups : r.ngroups % round;
-        if (4 * rest <= 4u * cus) full -= rest;
+        quad = full > rest && 4 * rest <= waves && rest <= (fold_joint_waves(CB) - 1) * cus;
+        if (quad || 4 * rest <= 4u * cus) full -= rest;
     }
     const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
     int e = 0;
@@ -52,6 +54,14 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
         hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * full, waves / nw, 0)), dim3(64 * nw), 0, s, r,
                            slot, 0u, 2 * full, false);
         e = (int)hipGetLastError();
+    }
+    if constexpr (per == 2) {
+        if (!e && full < r.ngroups && quad) {
+            hipLaunchKernelGGL((halves_quad_kernel<CB, true>), dim3(r.ngroups - full), dim3(256), 0, s, r, slot, 2 * full,
+                               2 * r.ngroups);
+            e = (int)hipGetLastError();
+            full = r.ngroups;
+        }
     }
     if (!e && full < r.ngroups) {
         hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * per * (r.ngroups - full), waves, 0)), dim3(64), 0,

@@ -159,3 +159,23 @@ def test_blinded_tile_and_group_edges(torch, ctx, bits, win, cap):
         ctx.set_grid_limit(0)
         ctx.set_window(bits, old[1])
         ctx.set_lanes(bits, *old[0])
+
+
+@pytest.mark.parametrize("bits,waves", [(1024, 3), (2048, 2)])
+def test_partial_round_a_wave_per_simd(torch, ctx, bits, waves):
+    """Past full rounds of one-lane blocks the last groups run a wave per SIMD, two units
+    per block: an odd number of groups and a last group of one tile, plain and blinded."""
+    import torch as t
+
+    n = 128 * t.cuda.get_device_properties(0).multi_processor_count * waves + 64 * 4 + 3
+    keys = keys_of(bits, 2)
+    km = (np.arange(n) >= n - 64 * 7).astype(np.uint32)
+    msg = inputs.make_message(n * (bits // 8 - 4) - 5, bits + 2)
+    ctx.load_keys(keys)
+    np.testing.assert_array_equal(roundtrip(torch, ctx, km, msg)[0], msg)
+    plan = ctx.plan(km, len(msg))
+    rblk = torch.from_numpy(inputs.make_blinding(keys, km, bits)).cuda()
+    got = plan.decrypt_blinded(*plan.encrypt_blinded(torch.from_numpy(msg).cuda(), rblk))
+    assert plan.check() == binding.PMK_OK
+    np.testing.assert_array_equal(got[: len(msg)].cpu().numpy(), msg)
+    plan.close()
