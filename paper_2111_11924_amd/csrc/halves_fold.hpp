@@ -3,6 +3,11 @@
 //
 // A block is two or four waves on as many tiles under one key, modulo one
 // prime, sharing the prime's table in LDS (fold_lane_block).
+//
+// Bound by VALU issue and, at full load, by the chip's power.  2048-bit keys, the
+// 12,288 jobs of the full rounds of 100 MiB: 48.3 ms, 64.4 with Montgomery
+// products (2.08 against 3.80 x 10^10 VALU instructions; the matrix cores are
+// 22 % busy, behind them).  16 MB: 4.9 / 4.5 ms at 1024 bits, 39.7 / 28.0 at 3072.
 #pragma once
 
 namespace pmk {
@@ -309,7 +314,7 @@ PMK_DEV void halves_fold_block(const ClassRun &r, uint64_t slot_words, uint32_t 
 
 // The partial round after full ones, as blocks of two units (group, h): four waves,
 // one on each SIMD, which blocks of one or two waves do not ensure after the full
-// rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 3.7
+// rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 4.5
 // ms here; 15 MB under 1024-bit keys 4.46 / 3.90 ms; from an idle chip blocks of one
 // wave are as even and 3 to 7 % faster).  table and entry hold two tables and four rows,
 // and fill LDS so that one block fewer fits a compute unit than the class has waves per SIMD.

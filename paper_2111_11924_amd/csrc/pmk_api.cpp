@@ -469,7 +469,8 @@ int pmk_decrypt_blinded_plan(pmk_plan *pl, const uint8_t *d_ct_star, const uint8
         ClassRun &r = pl->runs[c];
         if (!r.ntiles) continue;
         // the one-pass form keeps two odd-power tables per slot
-        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], 2 * table_words(c, 0, r.slots_dec, r.ntiles, r.win));
+        const uint64_t need = 2ull * r.slots_dec * table_words_per_slot(c, 1, r.win);
+        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], need);
         if (te != hipSuccess) return hip_err(ctx, te, "window table allocation");
         r.table_words = pl->table_cap[c];
     }
@@ -573,14 +574,33 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
     auto pack = [&](int c, void *s) {
         return timed_launch(pl, PMK_KERNEL_PACK, s, [&] { return launch_pack(pl->runs[c], in, decrypt, s); });
     };
-    int lanes = total && nl ? 2 : 1;
+    int lanes = total && nl ? 2 : 1, own = 1;  // streams; of the ordered classes, those on `stream`
+    int alone = 0;  // and those among them that fill the chip
     if (decrypt) {
         auto work = [&](int c) {
             const double s = kClassBits[c] / 64.0;
             return (double)pl->runs[c].ntiles * kClassBits[c] * (2 * s * s + s);
         };
         std::sort(order, order + nl, [&](int x, int y) { return work(x) > work(y); });
-        lanes = std::min(nl, 3);  // one side stream measured 5 ms more (58.3 / 53.0 ms at 25 MiB in 4 classes)
+        // Classes too large for the group form beside the others fill the chip by
+        // themselves: they follow one another on `stream`, as pmk_decrypt_plan
+        // launches them, largest first, and the small ones run beside them.  Without
+        // any, or where all together leave SIMDs idle, all run side by side.  25 MiB
+        // in four classes: 57.6 ms one after another; on three streams 54 to 70, as
+        // 4096-bit blocks, which need whole compute units, are placed before or after
+        // the others' (60.4 with Montgomery products).  3 MB: 16.4 and 12.6 ms.
+        auto fills = [&](int c) {
+            ClassRun r = pl->runs[c];
+            r.share = (uint32_t)nl;
+            return fold_group(kClassBits[c]).nl && !group_launch(r, (uint32_t)ctx->num_cus);
+        };
+        double load = 0;  // of the SIMDs' waves, one lane per number
+        for (int i = 0; i < nl; ++i)
+            load += 2.0 * pl->runs[order[i]].ntiles / (4.0 * ctx->num_cus * fold_lane_waves(kClassBits[order[i]]));
+        own = load > 1 ? (int)(std::stable_partition(order, order + nl, fills) - order) : 0;
+        if (own == 0) own = std::min(nl, 1);
+        else alone = own;
+        lanes = 1 + std::min(nl - own, 2);
     } else {
         for (int c = kNumClasses - 1; c >= 0 && !e; --c)
             if (pl->runs[c].ntiles) e = pack(c, stream);
@@ -590,9 +610,8 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
         for (int i = 0; i < lanes - 1 && !e; ++i) e = hipStreamWaitEvent(pl->side_stream[i], pl->fork_event, 0);
     }
     auto stream_of = [&](int lane) { return lane == 0 ? stream : (void *)pl->side_stream[lane - 1]; };
-    // the largest class's packing and halves on `stream`, the others on the side
-    // streams, packed meanwhile, so that its blocks are placed first
-    for (int i = 0; i < nl && decrypt && !e; ++i) e = pack(order[i], stream_of(i < lanes ? i : lanes - 1));
+    auto lane_of = [&](int i) { return i < own ? 0 : std::min(i - own + 1, lanes - 1); };
+    for (int i = 0; i < nl && decrypt && !e; ++i) e = pack(order[i], stream_of(lane_of(i)));
     if (!e && !decrypt && total) {
         void *s = stream_of(lanes - 1);
         const uint32_t grid = persistent_grid(total, pl->batch_slots, ctx->grid_limit);
@@ -601,7 +620,7 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
     for (int i = 0; i < nl && !e; ++i) {
         ClassRun r = pl->runs[order[i]];
         r.win = ctx->win[order[i]];
-        if (decrypt && nl > 1) {
+        if (decrypt && nl > 1 && i >= alone) {
             // classes side by side share the chip (group_launch); one lane per
             // number otherwise, since together they fill it, and a class's last
             // partial round stays in its launch, where its waves start as soon as
@@ -610,7 +629,7 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
             if (!fold_group(kClassBits[order[i]]).nl) r.fill_lanes = 1;
             r.tail_lanes = 0;
         }
-        void *s = decrypt ? stream_of(i < lanes ? i : lanes - 1) : stream;
+        void *s = decrypt ? stream_of(lane_of(i)) : stream;
         e = timed_launch(pl, decrypt ? PMK_KERNEL_CRT_HALVES : PMK_KERNEL_ENCRYPT, s, [&] {
             return decrypt ? launch_decrypt_halves(r, s) : launch_encrypt(r, s);
         });
