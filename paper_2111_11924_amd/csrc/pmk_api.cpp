@@ -539,15 +539,14 @@ int pmk_plan_kernel_time(pmk_plan *pl, int kind, double *ms_total, uint64_t *lau
 
 namespace pmk {
 
-// Launches of one pass of the batched path.  Packing runs on `stream`; then
+// Launches of one pass of the batched path.  After packing
 // the exponentiation kernels of the size classes run side by side on `stream`
 // and the plan's side streams (forked and joined with events), so that
 // classes too small to fill the chip share it:
 //   encryption: the 4096- and 3072-bit classes as one persistent work-queue
 //     launch on a side stream, the one-lane classes on `stream`, largest first;
-//   decryption: each class's CRT-halves kernel, classes ordered by their work:
-//     the two largest on streams of their own, the others in that order on a
-//     third.
+//   decryption: each class's CRT-halves launch; classes that fill the chip by
+//     themselves one after another on `stream`, the others beside them.
 // Garner recombination and unpacking follow on `stream`.
 int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, void *stream) {
     pmk_ctx *ctx = pl->ctx;
