@@ -312,6 +312,39 @@ PMK_DEV void halves_fold_block(const ClassRun &r, uint64_t slot_words, uint32_t 
     }
 }
 
+// Blocks of the lane form's kernel fn resident on a compute unit, by their waves:
+// a block's table takes its LDS whatever its waves, and its waves their SIMDs
+// together (4096 bits: 256 blocks of three waves at a time on 256 compute units,
+// where 1,024 waves / 3 = 341 dealt 512 units in three rounds, 88 ms, for two).
+template <int CB>
+struct FoldBlocks {
+    uint32_t n[fold_lane_block(CB) + 1] = {};
+    explicit FoldBlocks(const void *fn) {
+        for (int w = 1; w <= fold_lane_block(CB); ++w) {
+            int nb = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 64 * w, 0) != hipSuccess || nb < 1) nb = 1;
+            n[w] = (uint32_t)nb;
+        }
+    }
+    // blocks of nw waves, at most `waves` waves
+    uint32_t resident(uint32_t nw, uint32_t waves, uint32_t cus) const {
+        const uint32_t b = n[nw] * cus;
+        return b < waves / nw ? b : waves / nw;
+    }
+};
+
+// Launches of groups of one tile each, in blocks of one wave: one launch per round
+// of a wave per SIMD (1024 bits: two), which an idle chip places evenly; in one
+// launch later blocks land where one ends, some SIMDs two deep (2,048 jobs of
+// 2048 bits: 12.5 ms in one launch, 8.9 here).
+template <int CB, typename Launch>
+int lone_rounds(uint32_t units, uint32_t grid, uint32_t cus, Launch launch) {
+    const uint32_t even = (CB > 1024 ? 4 : 8) * cus, round = grid < even ? grid : even;
+    int e = 0;
+    for (uint32_t u = 0; u < units && !e; u += round) e = launch(u, units - u < round ? units : u + round);
+    return e;
+}
+
 // The partial round after full ones, as blocks of two units (group, h): four waves,
 // one on each SIMD, which blocks of one or two waves do not ensure after the full
 // rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 4.5

@@ -22,16 +22,9 @@ int launch_joint_lane_class(const ClassRun &r, hipStream_t s);
 template <int CB>
 int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     constexpr uint32_t per = fold_lane_block(CB);
-    static const uint32_t occ = [] {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)halves_joint_kernel<CB>, kJointBlock<CB>, 0) !=
-                hipSuccess ||
-            nb < 1)
-            nb = 1;
-        return (uint32_t)nb;
-    }();
+    static const FoldBlocks<CB> occ((const void *)halves_joint_kernel<CB>);
     const uint32_t cus = (uint32_t)device_cus();
-    uint32_t waves = per * occ * cus;
+    uint32_t waves = per * occ.n[per] * cus;
     if (r.grid_cap && r.grid_cap < waves) waves = r.grid_cap;
     if (eight_lanes(CB) && 2 * r.ntiles < waves && r.slots_dec >= 4 * r.ntiles) {
         uint32_t lane_units = 0;
@@ -40,7 +33,8 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     }
     if (r.slots_dec < waves) waves = r.slots_dec;
     const uint32_t nw = waves < r.group_tiles ? waves : r.group_tiles;
-    const uint32_t round = waves / (2 * per) ? waves / (2 * per) : 1;  // groups
+    const uint32_t grid = occ.resident(nw, waves, cus);
+    const uint32_t round = grid / 2 ? grid / 2 : 1;  // groups
     uint32_t full = r.ngroups;
     bool quad = false;
     if (per == 2 && waves >= 2) {
@@ -49,11 +43,18 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
         if (quad || 4 * rest <= 4u * cus) full -= rest;
     }
     const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
+    auto blocks = [&](uint32_t from, uint32_t to, uint32_t n, uint32_t threads, bool split) {
+        hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(to - from, n, 0)), dim3(threads), 0, s, r, slot, from,
+                           to, split);
+        return (int)hipGetLastError();
+    };
     int e = 0;
-    if (full) {
-        hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * full, waves / nw, 0)), dim3(64 * nw), 0, s, r,
-                           slot, 0u, 2 * full, false);
-        e = (int)hipGetLastError();
+    if (r.group_tiles == 1) {
+        e = lone_rounds<CB>(2 * r.ngroups, grid, cus,
+                            [&](uint32_t from, uint32_t to) { return blocks(from, to, grid, 64, false); });
+        full = r.ngroups;
+    } else if (full) {
+        e = blocks(0, 2 * full, grid, 64 * nw, false);
     }
     if constexpr (per == 2) {
         if (!e && full < r.ngroups && quad) {
@@ -63,11 +64,7 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
             full = r.ngroups;
         }
     }
-    if (!e && full < r.ngroups) {
-        hipLaunchKernelGGL(halves_joint_kernel<CB>, dim3(persistent_grid(2 * per * (r.ngroups - full), waves, 0)), dim3(64), 0,
-                           s, r, slot, 2 * per * full, 2 * per * r.ngroups, true);
-        e = (int)hipGetLastError();
-    }
+    if (!e && full < r.ngroups) e = blocks(2 * per * full, 2 * per * r.ngroups, waves, 64, true);
     if (e) return e;
     hipLaunchKernelGGL(blind_check_kernel<CB>, dim3(2 * r.ntiles), dim3(64), 0, s, r);
     e = (int)hipGetLastError();

@@ -1,0 +1,67 @@
+"""Decryption under many keys with few tiles each: groups of one to three tiles, in
+every form that such a launch takes, past one round of its blocks, each key
+another.  Exact: the message comes back, plain, batched and blinded."""
+import numpy as np
+import pytest
+
+from paper_2111_11924_amd import binding, inputs
+from perf import cases
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    c = binding.Context(0)
+    yield c
+    c.close()
+
+
+def keys_of(bits, count):
+    """`count` keys: the pairs of a short list of primes, repeated where it has fewer,
+    neighbours always different."""
+    pairs = cases._pairs(bits)
+    return [cases._key(bits, *pairs[i * 7 % len(pairs)]) for i in range(count)]
+
+
+def check(ctx, bits, keys, chunks, blinded, mixed=0):
+    import torch
+
+    ks = keys_of(bits, keys)
+    counts = np.full(keys, chunks)
+    if mixed:  # groups of different sizes
+        counts[::3] += mixed
+    km = np.repeat(np.arange(keys, dtype=np.uint32), counts)
+    msg = inputs.make_message(len(km) * (bits // 8 - 4) - 5, bits + keys)
+    ctx.load_keys(ks)
+    plan = ctx.plan(km, len(msg))
+    d = torch.from_numpy(msg).cuda()
+    if blinded:
+        r = inputs.make_message(len(km) * (bits // 8), 9).reshape(len(km), bits // 8).copy()
+        r[:, 0] = 0
+        outs = [plan.decrypt_blinded(*plan.encrypt_blinded(d, torch.from_numpy(r.reshape(-1)).cuda()))]
+    else:
+        ct = plan.encrypt(d)
+        outs = [plan.decrypt(ct), plan.decrypt(ct, batch=True)]
+    assert plan.check() == binding.PMK_OK
+    for o in outs:
+        np.testing.assert_array_equal(o[: len(msg)].cpu().numpy(), msg)
+    plan.close()
+
+
+# one tile per key: past a wave per SIMD (1024, 2048), past three blocks (3072) and one
+# block (4096) per compute unit; two and three tiles; groups of mixed sizes
+@pytest.mark.parametrize("bits,keys,chunks,mixed", [
+    (1024, 520, 33, 0), (1024, 522, 129, 0), (2048, 520, 20, 0), (2048, 140, 129, 70), (3072, 390, 20, 0),
+    (3072, 260, 65, 0), (3072, 130, 129, 64), (4096, 130, 17, 0), (4096, 131, 65, 0), (4096, 90, 129, 64)])
+def test_few_tiles_per_key(ctx, bits, keys, chunks, mixed):
+    check(ctx, bits, keys, chunks, False, mixed)
+
+
+@pytest.mark.parametrize("bits,keys,chunks,mixed", [
+    (1024, 522, 129, 0), (2048, 520, 20, 0), (3072, 390, 20, 0), (3072, 130, 129, 64), (4096, 131, 65, 0)])
+def test_few_tiles_per_key_blinded(ctx, bits, keys, chunks, mixed):
+    check(ctx, bits, keys, chunks, True, mixed)
