@@ -35,7 +35,7 @@ LIB = os.path.join(PKG, "libpmk.so")
 PROBE = os.path.join(ROOT, "_build", "mad_rate")  # VALU issue-rate probe (python -m paper_2111_11924_amd.peak)
 
 SOURCES = ["k8192.hip", "k6144.hip", "kbatch.hip", "k4096.hip", "k3072.hip", "k2048.hip", "k1024.hip", "k512.hip", "k256.hip", "k128.hip",
-           "kfold.hip", "kg1024.hip", "kg2048.hip", "kg3072.hip", "kg4096.hip", "kg6144.hip", "kg8192.hip", "kprime.hip", "kmp.hip", "kjoint.hip", "klanes.hip", "kjlanes.hip", "noalloc.hip", "dispatch.cpp", "pmk_api.cpp", "mp_api.cpp", "keyprep.cpp", "server.cpp"]
+           "kfold.hip", "kg1024.hip", "kg2048.hip", "kg3072.hip", "kg4096.hip", "kg6144.hip", "kg8192.hip", "kjmont.hip", "km4096.hip", "km3072.hip", "km2048.hip", "km1024.hip", "kprime.hip", "kmp.hip", "kjoint.hip", "klanes.hip", "kjlanes.hip", "noalloc.hip", "dispatch.cpp", "launch_rule.cpp", "pmk_api.cpp", "mp_api.cpp", "keyprep.cpp", "server.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -53,7 +53,8 @@ PADS = os.path.join(CSRC, "code_pad.json")
 # kernel kinds: the numbers of CodeKind in kernels_impl.hpp
 CODE_KIND = {"encrypt_kernel": 1, "halves_kernel": 2, "halves_joint_kernel": 3, "halves_lanes_kernel": 4,
              "halves_lanes_joint_kernel": 5, "garner_kernel": 6, "garner_lds_kernel": 7, "batch_wide_kernel": 8,
-             "mp_part_kernel": 9, "mp_garner_kernel": 10, "miller_rabin_kernel": 11}
+             "mp_part_kernel": 9, "mp_garner_kernel": 10, "miller_rabin_kernel": 11,
+             "halves_mont_kernel": 12, "halves_joint_mont_kernel": 13}
 
 
 def _headers_mtime() -> float:

@@ -53,6 +53,9 @@ int launch_encrypt(const ClassRun &r, void *stream) {
 }
 int launch_decrypt_halves(const ClassRun &r, void *stream) {
     if (r.ntiles == 0) return 0;
+    const uint32_t cus = (uint32_t)device_cus();
+    if (group_launch(r, cus)) return launch_halves_group(r, 0, stream);
+    if (mont_launch(r, cus)) return launch_mont(r, stream);
     PMK_DISPATCH(r.cls, launch_halves, r, (hipStream_t)stream);
 }
 int launch_garner(const ClassRun &r, void *stream) {
@@ -78,6 +81,28 @@ uint32_t exp_units(int cls, int decrypt, uint32_t ntiles) {
     // one wavefront per 64 / L chunks: encryption per tile, CRT halves per tile and prime
     const int bits = kClassBits[cls];
     return decrypt ? 2 * ntiles * (uint32_t)lanes_half(bits) : ntiles * (uint32_t)lanes_full(bits);
+}
+
+#define PMK_MONT(B)                                   \
+    int launch_mont_##B(const ClassRun &, hipStream_t); \
+    uint32_t mont_resident_##B();
+PMK_MONT(1024)
+PMK_MONT(2048)
+PMK_MONT(3072)
+PMK_MONT(4096)
+
+#define PMK_DISPATCH_MONT(cls, FN, none, ...)      \
+    switch (kClassBits[cls]) {                     \
+        case 1024: return FN##_1024(__VA_ARGS__);  \
+        case 2048: return FN##_2048(__VA_ARGS__);  \
+        case 3072: return FN##_3072(__VA_ARGS__);  \
+        case 4096: return FN##_4096(__VA_ARGS__);  \
+        default: return none;                      \
+    }
+
+uint32_t mont_resident(int cls) { PMK_DISPATCH_MONT(cls, mont_resident, 0u) }
+int launch_mont(const ClassRun &r, void *stream) {
+    PMK_DISPATCH_MONT(r.cls, launch_mont, (int)hipErrorInvalidValue, r, (hipStream_t)stream)
 }
 
 #define PMK_GROUP(B)                                     \
@@ -109,11 +134,25 @@ int launch_halves_group(const ClassRun &r, uint32_t first, void *stream) {
     PMK_DISPATCH_GROUP(r.cls, launch_halves_group, (int)hipErrorInvalidValue, r, first, (hipStream_t)stream)
 }
 
-uint64_t table_words(int cls, uint32_t slots_enc, uint32_t slots_dec, uint32_t ntiles, int win) {
-    uint64_t need = slots_enc * table_words_per_slot(cls, 0, 0);
-    need = std::max(need, slots_dec * table_words_per_slot(cls, 1, win));
-    if (fold_group(kClassBits[cls]).nl)
-        need = std::max(need, std::min<uint64_t>(8ull * ntiles, group_resident(cls)) * group_slot_words(cls, win));
+uint64_t table_words(const ClassRun &r_) {
+    ClassRun r = r_;
+    r.table_words = 0;  // whatever the form needs, not what fits the present table
+    const uint64_t slot = table_words_per_slot(r.cls, 1, r.win);
+    uint64_t need = std::max(r.slots_enc * table_words_per_slot(r.cls, 0, 0), r.slots_dec * slot);
+    if (fold_group(kClassBits[r.cls]).nl)
+        need = std::max(need, std::min<uint64_t>(8ull * r.ntiles, group_resident(r.cls)) * group_slot_words(r.cls, r.win));
+    if (mont_launch(r, (uint32_t)device_cus()))
+        need = std::max(need, std::min<uint64_t>(2ull * r.ntiles, mont_resident(r.cls)) * slot);
+    return need;
+}
+
+uint64_t joint_table_words(const ClassRun &r_) {
+    ClassRun r = r_;
+    r.table_words = 0;
+    const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
+    uint64_t need = r.slots_dec * slot;
+    if (joint_mont_launch(r, (uint32_t)device_cus()))
+        need = std::max(need, std::min<uint64_t>(2ull * r.ntiles, joint_mont_resident(r.cls)) * slot);
     return need;
 }
 

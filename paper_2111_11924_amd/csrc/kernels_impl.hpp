@@ -45,7 +45,8 @@ namespace pmk {
 // same numbers as the build's table:
 enum CodeKind : uint32_t {
     kCodeEncrypt = 1, kCodeHalves = 2, kCodeJoint = 3, kCodeLanes = 4, kCodeJointLanes = 5, kCodeGarner = 6,
-    kCodeGarnerLds = 7, kCodeBatchWide = 8, kCodeMpPart = 9, kCodeMpGarner = 10, kCodeMillerRabin = 11
+    kCodeGarnerLds = 7, kCodeBatchWide = 8, kCodeMpPart = 9, kCodeMpGarner = 10, kCodeMillerRabin = 11,
+    kCodeHalvesMont = 12, kCodeJointMont = 13
 };
 #ifndef PMK_CODE_PAD
 #define PMK_CODE_PAD 0u
@@ -486,22 +487,34 @@ PMK_DEV void halves_unit(const ClassRun r, uint32_t jt, uint32_t *tbl, uint32_t 
     const uint32_t *one_h = hr + G.h_one;
 
     uint32_t acc[NL], b[NL];
-    uint32_t w[S];
+    if constexpr (S <= 64) {
+        uint32_t w[S];
 #pragma unroll
-    for (int k = 0; k < S; ++k) w[k] = r.x32[((size_t)tile * S + k) * kTile + lane];
-    if (h == 0 && r.desc[(size_t)tile * kTile + lane].msg_len) {
-        // C must lie in Z_N: compare with N, most significant word first
-        const uint32_t *n32 = kr + G.off_n32;
-        int cmp = 0;
+        for (int k = 0; k < S; ++k) w[k] = r.x32[((size_t)tile * S + k) * kTile + lane];
+        if (h == 0 && r.desc[(size_t)tile * kTile + lane].msg_len) {
+            // C must lie in Z_N: compare with N, most significant word first
+            const uint32_t *n32 = kr + G.off_n32;
+            int cmp = 0;
 #pragma unroll
-        for (int k = S - 1; k >= 0; --k) cmp = cmp ? cmp : (w[k] > n32[k]) - (w[k] < n32[k]);
-        if (cmp >= 0) atomicOr(r.err, 1u);
+            for (int k = S - 1; k >= 0; --k) cmp = cmp ? cmp : (w[k] > n32[k]) - (w[k] < n32[k]);
+            if (cmp >= 0) atomicOr(r.err, 1u);
+        }
+#pragma unroll
+        for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j + NL);
+        store_row4(tbl, 0, lane, acc);  // c_hi, parked in entry 0 until it is used
+#pragma unroll
+        for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j);
+    } else {
+        // 3072/4096 bits: the ciphertext words are read from the tile in memory
+        // (staging up to 128 words in registers would spill); unpacking checks
+        // that C lies in Z_N
+        const uint32_t *w = fresh_v(r.x32 + (size_t)tile * S * kTile + lane);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) acc[j] = radix_limb_mem<S, LB>(w, kTile, j + NL);
+        store_row4(tbl, 0, lane, acc);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) acc[j] = radix_limb_mem<S, LB>(w, kTile, j);
     }
-#pragma unroll
-    for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j + NL);
-    store_row4(tbl, 0, lane, acc);  // c_hi, parked in entry 0 until it is used
-#pragma unroll
-    for (int j = 0; j < NL; ++j) acc[j] = radix_limb<S, LB>(w, j);
     load_limbs(b, hr + G.h_rr);
 
     const int TH = 1 << (win - 1);  // odd powers x~, x~^3, ..., x~^(2 TH - 1)

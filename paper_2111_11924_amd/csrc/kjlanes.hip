@@ -1,7 +1,7 @@
 // Blinded decryption (one pass per prime, Sec. 3.1) in lane groups
 // (halves_lanes_joint_kernel) for the part of a launch that leaves SIMDs idle:
 // 128- to 512-bit keys with 2 or 4 lanes per number and small launches of 2048- (8
-// lanes) and 3072- to 4096-bit keys (4 or 8), where the fold form is not faster, as
+// lanes), 3072- (4 or 8) and 4096-bit keys (2, 4 or 8), where no other form is faster, as
 // lanes_for_launch decides; the lane-group classes (6144/8192) with 8 instead of 4
 // as wide_fill decides.  A translation unit of its own, so the other
 // objects stay as they are and the classes compile in parallel with them.
@@ -43,7 +43,7 @@ int launch_class(const ClassRun &r, uint32_t jt_begin, uint32_t jt_end, hipStrea
 template <int CB>
 int launch_L(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, hipStream_t s) {
     if constexpr (lanes_half(CB) == 1) {
-        if constexpr (CB <= 512)
+        if constexpr (CB <= 512 || CB == 4096)
             if (L == 2) return launch_class<CB, 2>(r, jt_begin, jt_end, s);
         if constexpr (CB <= 512 || CB >= 3072)
             if (L == 4) return launch_class<CB, 4>(r, jt_begin, jt_end, s);
@@ -68,6 +68,7 @@ uint32_t joint_lanes_resident(int cls, int L) {
         case 4 * 16 + 8: return resident_of<2048, 8>();
         case 5 * 16 + 4: return resident_of<3072, 4>();
         case 5 * 16 + 8: return resident_of<3072, 8>();
+        case 6 * 16 + 2: return resident_of<4096, 2>();
         case 6 * 16 + 4: return resident_of<4096, 4>();
         case 6 * 16 + 8: return resident_of<4096, 8>();
         case 7 * 16 + 2 * lanes_half(6144): return resident_of<6144, 2 * lanes_half(6144)>();

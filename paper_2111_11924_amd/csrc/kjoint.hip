@@ -18,7 +18,8 @@ int launch_joint_lane_class(const ClassRun &r, hipStream_t s);
 // Montgomery products, 22.1 ms here).  A small launch runs over lane groups instead
 // while each of their waves has a SIMD of its own: eight lanes take 4.6 / 10.0 / 20.5
 // ms at 2048 / 3072 / 4096 bits against 5.1 / 17.4 / 40.6 in one lane; four lanes pay
-// at 3072 (12.1 ms) and 4096 bits, no longer at 2048 (5.3 ms), two at none (4096: 45 ms).
+// at 3072 (12.1 ms) and 4096 bits, no longer at 2048 (5.3 ms), two at 4096 where the
+// shared tables make two rounds (joint_two_lanes).
 template <int CB>
 int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     constexpr uint32_t per = fold_lane_block(CB);
@@ -29,8 +30,9 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     if (eight_lanes(CB) && 2 * r.ntiles < waves && r.slots_dec >= 4 * r.ntiles) {
         uint32_t lane_units = 0;
         const int L = lanes_for_launch(r, 2 * r.ntiles, waves, 4u * cus, joint_lanes_resident, &lane_units);
-        if (L > 1) return launch_joint_lanes(r, L, 0, 2 * r.ntiles, s);
+        if (L > 2 || (L == 2 && joint_two_lanes(r, cus))) return launch_joint_lanes(r, L, 0, 2 * r.ntiles, s);
     }
+    if (joint_mont_launch(r, cus)) return launch_joint_mont(r, s);
     if (r.slots_dec < waves) waves = r.slots_dec;
     const uint32_t nw = waves < r.group_tiles ? waves : r.group_tiles;
     const uint32_t grid = occ.resident(nw, waves, cus);

@@ -1,0 +1,152 @@
+// Which form the CRT halves of a launch take.  Each rule estimates the forms'
+// times from the rounds of waves or blocks that the launch makes and takes the
+// shortest.  Times in ms, measured on 256 compute units (loads are scaled to the
+// device's number of them).
+#include <algorithm>
+
+#include "pmk_internal.hpp"
+
+namespace pmk {
+
+namespace {
+
+// Time of `load` (waves, blocks or units) in rounds of `full`, or of `room` where
+// the table or the grid limit holds fewer.  A round that leaves SIMDs with fewer waves
+// takes less: part[i] up to (i + 1) / N of a full one.
+template <int N>
+double rounds_ms(uint64_t load, uint64_t full, uint64_t room, const double (&part)[N]) {
+    auto one = [&](uint64_t x) { return part[(x * N - 1) / full]; };
+    const uint64_t round = std::max<uint64_t>(1, std::min(full, room)), rest = load % round;
+    return (double)(load / round) * one(round) + (rest ? one(rest) : 0);
+}
+
+// Slots of `slot` words in the launch's table (0 words: not sized yet), at most the
+// grid limit.
+uint64_t room_of(const ClassRun &r, uint64_t slot) {
+    const uint64_t room = r.table_words ? r.table_words / slot : ~0ull;
+    return r.grid_cap ? std::min<uint64_t>(room, r.grid_cap) : room;
+}
+
+// Fold form in one lane, units of nw waves (tiles of a group, modulo one prime).  A
+// group's table takes LDS whatever its tiles: three 3072-bit blocks or one
+// 4096-bit block fit a compute unit, so that small groups leave SIMDs idle there.
+double lane_ms(int bits, uint32_t nw, uint64_t units, uint64_t room, uint32_t cus) {
+    const uint64_t cu = cus;
+    switch (bits) {
+        case 1024:
+            if (nw == 1) return rounds_ms(units, 8 * cu, room, {1.1, 2.4});
+            return rounds_ms(units, 6 * cu, room, {1.1, 1.9, 2.75});
+        case 2048:
+            if (nw == 1) return rounds_ms(units, 4 * cu, room, {4.4});
+            return rounds_ms(units, 4 * cu, room, {4.4, 8.1});
+        case 3072:
+            if (nw == 1) return rounds_ms(units, 3 * cu, room, {14.3, 14.3, 15.8});
+            if (nw == 2) return rounds_ms(units, 2 * cu, room, {15.0, 24.4});
+            if (nw == 3) return rounds_ms(units, 2 * cu, room, {16.0, 29.5});
+            return rounds_ms(units, 2 * cu, room, {17.9, 32.0});
+        default: return rounds_ms(units, cu, room, {nw > 3 ? 31.0 : 28.9});
+    }
+}
+// The same, blinded.
+double joint_lane_ms(int bits, uint32_t nw, uint64_t units, uint64_t room, uint32_t cus) {
+    const uint64_t cu = cus;
+    switch (bits) {
+        case 1024:
+            if (nw == 1) return rounds_ms(units, 8 * cu, room, {1.45, 2.45});
+            return rounds_ms(units, 4 * cu, room, {1.45, 2.4});
+        case 2048:
+            if (nw == 1) return rounds_ms(units, 4 * cu, room, {5.9});
+            return rounds_ms(units, 4 * cu, room, {5.9, 11.2});
+        case 3072:
+            if (nw == 1) return rounds_ms(units, 3 * cu, room, {17.6, 17.6, 20.5});
+            if (nw == 2) return rounds_ms(units, 2 * cu, room, {18.5, 29.3});
+            if (nw == 3) return rounds_ms(units, 2 * cu, room, {19.5, 35.0});
+            return rounds_ms(units, 2 * cu, room, {22.0, 38.7});
+        default: return rounds_ms(units, cu, room, {nw > 3 ? 42.8 : (nw > 2 ? 39.0 : 37.5)});
+    }
+}
+
+// Montgomery products: one lane per number up to 4096 bits, four above.
+double mont_ms(int bits, uint64_t jobs, uint64_t room, uint32_t cus) {
+    const uint64_t cu = cus;
+    switch (bits) {
+        case 1024: return rounds_ms(jobs, 12 * cu, room, {1.14, 2.06, 2.92});
+        case 2048: return rounds_ms(jobs, 12 * cu, room, {5.76, 11.3, 16.5});
+        case 3072: return rounds_ms(jobs, 8 * cu, room, {18.8, 36.0});
+        case 4096: return rounds_ms(jobs, 8 * cu, room, {44.7, 85.5});
+        // 4 waves per job; a partial round after a full one runs beside its last waves
+        case 6144:
+            if (jobs < 2 * cu) return rounds_ms(jobs, 2 * cu, room / 4, {67.0, 111.5});
+            return rounds_ms(jobs, 2 * cu, room / 4, {46.0, 66.0, 111.5, 111.5});
+        default:
+            if (jobs < 2 * cu) return rounds_ms(jobs, 2 * cu, room / 4, {146.0, 154.0, 258.0, 258.0});
+            return rounds_ms(jobs, 2 * cu, room / 4, {107.0, 154.0, 258.0, 258.0});
+    }
+}
+double joint_mont_ms(int bits, uint64_t jobs, uint64_t room, uint32_t cus) {
+    const uint64_t cu = cus;
+    switch (bits) {
+        case 1024: return rounds_ms(jobs, 8 * cu, room, {1.64, 2.84});
+        case 2048: return rounds_ms(jobs, 8 * cu, room, {7.2, 13.9});
+        case 3072: return rounds_ms(jobs, 8 * cu, room, {23.2, 43.8});
+        default: return rounds_ms(jobs, 8 * cu, room, {50.6, 50.6, 57.0, 57.0, 107.0, 107.0, 107.0, 107.0});
+    }
+}
+
+// A number over a block (halves_group_kernel): blocks of 16 chunks modulo one
+// prime.  Its chain is 2 to 5 times shorter than the one-lane chain, but it takes
+// more of the chip per number.
+double group_ms(int bits, uint64_t blocks, uint32_t cus) {
+    const uint64_t cu = cus, all = ~0ull;
+    switch (bits) {
+        case 1024: return rounds_ms(blocks, 8 * cu, all, {0.85, 0.92, 1.4, 1.77});
+        case 2048: return rounds_ms(blocks, 4 * cu, all, {2.7, 3.05});
+        case 3072: return rounds_ms(blocks, 2 * cu, all, {3.65, 4.5});
+        case 4096: return rounds_ms(blocks, 2 * cu, all, {6.3, 8.1});
+        case 6144: return rounds_ms(blocks, cu, all, {15.2});
+        default: return rounds_ms(blocks, cu, all, {39.2, 46.5});
+    }
+}
+
+}  // namespace
+
+bool mont_launch(const ClassRun &r, uint32_t cus) {
+    const int bits = kClassBits[r.cls];
+    if (!fold_lane(bits).nl) return false;
+    const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
+    return mont_ms(bits, 2ull * r.ntiles, room, cus) <
+           lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus);
+}
+
+bool group_launch(const ClassRun &r, uint32_t cus) {
+    const int bits = kClassBits[r.cls];
+    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits)) return false;
+    const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
+    double other = mont_ms(bits, 2ull * r.ntiles, room, cus);
+    if (fold_lane(bits).nl)
+        other = std::min(other, lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus));
+    // classes side by side share the chip
+    return group_ms(bits, 2ull * r.parts * std::max(1u, r.share), cus) < other;
+}
+
+bool group_rest(int bits, uint32_t groups, uint32_t cus) {
+    const uint64_t per = fold_lane_block(bits);
+    return group_ms(bits, 8 * per * groups, cus) < lane_ms(bits, (uint32_t)per, 2ull * groups, ~0ull, cus);
+}
+
+bool joint_mont_launch(const ClassRun &r, uint32_t cus) {
+    const int bits = kClassBits[r.cls];
+    if (!fold_lane(bits).nl) return false;
+    const uint64_t room = room_of(r, 2 * table_words_per_slot(r.cls, 1, r.win));
+    return joint_mont_ms(bits, 2ull * r.ntiles, room, cus) <
+           joint_lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus);
+}
+
+// At 4096 bits 44.8 ms while each of its waves has a SIMD.
+bool joint_two_lanes(const ClassRun &r, uint32_t cus) {
+    const uint64_t jobs = 2ull * r.ntiles, units = 2ull * r.ngroups;
+    return kClassBits[r.cls] == 4096 && 44.8 < std::min(joint_mont_ms(4096, jobs, ~0ull, cus),
+                                                        joint_lane_ms(4096, r.group_tiles, units, ~0ull, cus));
+}
+
+}  // namespace pmk

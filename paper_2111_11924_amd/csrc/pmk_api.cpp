@@ -110,8 +110,7 @@ hipError_t ensure_tables(pmk_plan *pl) {
         r.grid_cap = pl->ctx->grid_limit;
         r.fill_lanes = pl->ctx->fill_lanes[c];
         r.tail_lanes = pl->ctx->tail_lanes[c];
-        const uint64_t need = table_words(c, r.slots_enc, r.slots_dec, r.ntiles, r.win);
-        const hipError_t e = regrow(pl, &r.table, pl->table_cap[c], need);
+        const hipError_t e = regrow(pl, &r.table, pl->table_cap[c], table_words(r));
         if (e != hipSuccess) return e;
         r.table_words = pl->table_cap[c];
     }
@@ -468,9 +467,7 @@ int pmk_decrypt_blinded_plan(pmk_plan *pl, const uint8_t *d_ct_star, const uint8
     for (int c = 0; c < kNumClasses; ++c) {
         ClassRun &r = pl->runs[c];
         if (!r.ntiles) continue;
-        // the one-pass form keeps two odd-power tables per slot
-        const uint64_t need = 2ull * r.slots_dec * table_words_per_slot(c, 1, r.win);
-        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], need);
+        const hipError_t te = regrow(pl, &r.table, pl->table_cap[c], joint_table_words(r));
         if (te != hipSuccess) return hip_err(ctx, te, "window table allocation");
         r.table_words = pl->table_cap[c];
     }

@@ -339,6 +339,28 @@ uint32_t tile_groups(const Vec &tile_key, uint32_t ntiles, int per, Vec &out) {
 // with c* at r.x32 and c_R at r.fin32; tables need 2 table_words_per_slot(cls, 1, win)
 // words per slot
 int launch_decrypt_joint(const ClassRun &r, void *stream);
+// Montgomery products in one lane, 1024- to 4096-bit classes: the CRT halves of a
+// launch (kmont.inc), blinded decryption (kjmont.hip), and the waves of each that are
+// resident on the current device (0: no such form)
+PMK_HD constexpr int mont_waves(int bits) { return bits >= 3072 ? 2 : 3; }  // per SIMD, plain halves
+int launch_mont(const ClassRun &r, void *stream);
+int launch_joint_mont(const ClassRun &r, void *stream);
+uint32_t mont_resident(int cls);
+uint32_t joint_mont_resident(int cls);
+// Job tiles of `r` in full rounds of `resident` one-wave blocks, then the partial
+// round as a launch of its own, whose waves spread over the SIMDs; no more blocks
+// than the table has slots of `slot` words or the grid limit allows.
+template <typename Launch>
+int launch_rounds(const ClassRun &r, uint64_t slot, uint32_t resident, Launch launch) {
+    uint64_t grid = r.table_words / slot < resident ? r.table_words / slot : resident;
+    if (r.grid_cap && r.grid_cap < grid) grid = r.grid_cap;
+    if (grid < 1) grid = 1;
+    const uint32_t units = 2 * r.ntiles, rest = (uint32_t)(units % grid);
+    int e = 0;
+    if (units > rest) e = launch((uint32_t)grid, 0u, units - rest);
+    if (!e && rest) e = launch(rest, units - rest, units);
+    return e;
+}
 // CRT halves of job tiles [jt_begin, jt_end) in lane groups of L lanes per
 // number: the 128- to 512-bit classes with L = 2 or 4 (klanes.hip)
 int launch_halves_lanes(const ClassRun &r, int L, uint32_t jt_begin, uint32_t jt_end, void *stream);
@@ -423,34 +445,20 @@ uint32_t table_units(int cls, uint32_t ntiles);
 uint64_t group_slot_words(int cls, int win);
 uint32_t group_resident(int cls);
 int launch_halves_group(const ClassRun &r, uint32_t first, void *stream);
-// Whether a CRT-halves launch takes that form: while its blocks (2 r.parts, each
-// 16 chunks modulo one prime) are few.  A block's chain is 2 to 5 times shorter
-// than the one-lane chain, but it takes more of the chip per number, so the
-// one-lane form wins once it fills the SIMDs.  Measured, group against one lane:
-//   1024 bits  0.80 / 0.96 ms up to 600 blocks, 1.10 / 1.0 ms at 1,008
-//   2048 bits  3.0 / 3.86 ms at 640 blocks, 5.9 / 4.0 ms at 2,000
-//   3072 bits  3.6 ms to 256 blocks, 4.35 ms more for every 512 / 13.4 ms to 1,024 tiles
-//   4096 bits  6.3 ms to 256 blocks, 8.1 ms more for every 512 / 28.3 ms to 128 groups
-//   6144 and 8192 bits against 4 lanes per number: 16 / 74 and 40 / 164 ms at 190,
-//   about even where the 4-lane form fills the chip
-// The limits lie where the two meet (256 compute units); classes side by side
-// share the chip.
-inline uint64_t group_limit(int bits, uint32_t cus) {
-    switch (bits) {
-        case 1024: return 3ull * cus;
-        case 2048: return 7ull * cus / 2;
-        case 3072: return 13ull * cus / 2;
-        case 4096: return 7ull * cus;
-        default: return ~0ull;
-    }
-}
-inline bool group_launch(const ClassRun &r, uint32_t cus) {
-    const int bits = kClassBits[r.cls];
-    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits)) return false;
-    return 2ull * r.parts * (r.share > 1 ? r.share : 1) <= group_limit(bits, cus);
-}
-// table words that a class's launches over ntiles tiles use
-uint64_t table_words(int cls, uint32_t slots_enc, uint32_t slots_dec, uint32_t ntiles, int win);
+// Which form a launch takes (launch_rule.cpp), by the forms' estimated times.
+// group_launch: CRT halves spread over blocks; mont_launch, joint_mont_launch:
+// otherwise, Montgomery products in one lane rather than the fold form (1024 to
+// 4096 bits; 6144 and 8192 bits have Montgomery products over 4 lanes); joint_two_lanes:
+// of a small blinded launch, two lanes per number rather than either; group_rest: the
+// last `groups` groups of tiles after full rounds of the lane form spread over blocks.
+bool group_launch(const ClassRun &r, uint32_t cus);
+bool mont_launch(const ClassRun &r, uint32_t cus);
+bool joint_mont_launch(const ClassRun &r, uint32_t cus);
+bool joint_two_lanes(const ClassRun &r, uint32_t cus);
+bool group_rest(int bits, uint32_t groups, uint32_t cus);
+// table words that a class's launches use: plain, and blinded decryption
+uint64_t table_words(const ClassRun &r);
+uint64_t joint_table_words(const ClassRun &r);
 // persistent batched exponentiation (kbatch.hip)
 int launch_batch(const BatchArgs &a, uint32_t grid, void *stream);
 int launch_counter_reset(uint32_t *counter, void *stream);

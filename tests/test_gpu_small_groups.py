@@ -65,3 +65,44 @@ def test_few_tiles_per_key(ctx, bits, keys, chunks, mixed):
     (1024, 522, 129, 0), (2048, 520, 20, 0), (3072, 390, 20, 0), (3072, 130, 129, 64), (4096, 131, 65, 0)])
 def test_few_tiles_per_key_blinded(ctx, bits, keys, chunks, mixed):
     check(ctx, bits, keys, chunks, True, mixed)
+
+
+# so many keys that Montgomery products are the faster form: one lane per number (1024 to
+# 4096 bits), four lanes (6144, 8192); blinded also two lanes (4096)
+@pytest.mark.parametrize("bits,keys,chunks", [(1024, 520, 65), (3072, 400, 33), (3072, 270, 65), (4096, 330, 49),
+                                              (6144, 257, 49), (8192, 130, 49)])
+def test_montgomery_form(ctx, bits, keys, chunks):
+    check(ctx, bits, keys, chunks, False)
+
+
+@pytest.mark.parametrize("bits,keys,chunks", [(3072, 400, 33), (4096, 140, 20), (4096, 257, 20)])
+def test_montgomery_form_blinded(ctx, bits, keys, chunks):
+    check(ctx, bits, keys, chunks, True)
+
+
+@pytest.mark.parametrize("bits,keys", [(3072, 400), (4096, 330)])
+def test_montgomery_form_edges(ctx, bits, keys):
+    """Blocks 0, 1, N - 1, a multiple of one prime, and one of N itself, which is flagged and
+    decrypts to zero bytes; the others equal c^d mod N."""
+    import torch
+
+    ks, kb, per = keys_of(bits, keys), bits // 8, 49
+    ctx.load_keys(ks)
+    km = np.repeat(np.arange(keys, dtype=np.uint32), per)
+    plan = ctx.plan(km, len(km) * (kb - 4))
+    plan.set_decrypt_output(binding.PMK_DEC_BLOCKS)
+    ct = np.zeros((len(km), kb), np.uint8)
+    at = [0, 1, 2, 3, per * keys - 1]
+    k, last = ks[0], ks[-1]
+    vals = [1, k.n - 1, k.p * 5, k.n, last.q * (last.p - 1)]
+    for i, v in zip(at, vals):
+        ct[i] = np.frombuffer(v.to_bytes(kb, "big"), np.uint8)
+    out = plan.decrypt(torch.from_numpy(ct.reshape(-1)).cuda())
+    assert plan.check() == binding.PMK_ERANGE
+    got = out[: ct.size].cpu().numpy().reshape(ct.shape)
+    want = np.zeros_like(ct)
+    for i, v in zip(at, vals):
+        key = ks[int(km[i])]
+        want[i] = np.frombuffer((0 if v >= key.n else pow(v, key.d, key.n)).to_bytes(kb, "big"), np.uint8)
+    np.testing.assert_array_equal(got, want)
+    plan.close()

@@ -1,0 +1,89 @@
+"""The rule that picks the form of a CRT-halves launch (csrc/launch_rule.cpp, built
+here for the host) against measured times: whatever it picks takes no more than
+6 % longer than the fastest form measured for that shape."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2111_11924_amd", "csrc")
+BITS = [128, 256, 512, 1024, 2048, 3072, 4096, 6144, 8192]
+
+# bits, keys, chunks per key: ms of the group form (G), the lane form (L) and
+# Montgomery products (M), 256 compute units; blinded: with two lanes per number (T)
+PLAIN = [
+    (1024, 64, 64, dict(G=0.86, L=1.06)), (1024, 256, 256, dict(G=4.58, L=1.96)),
+    (1024, 1024, 64, dict(L=2.82, M=2.06)), (1024, 512, 192, dict(L=3.68, M=2.93)),
+    (2048, 64, 64, dict(G=2.72, M=5.41)), (2048, 256, 64, dict(G=5.91, L=4.07, M=5.45)),
+    (2048, 1024, 64, dict(L=8.89, M=11.3)), (2048, 256, 256, dict(G=23.4, L=8.35)),
+    (3072, 64, 64, dict(G=4.57, M=17.8)), (3072, 256, 64, dict(G=17.7, L=14.2, M=17.9)),
+    (3072, 256, 96, dict(L=24.35, M=18.7)), (3072, 256, 192, dict(L=29.5, M=36.0)),
+    (3072, 512, 64, dict(L=37.9, M=18.8)), (3072, 512, 128, dict(L=45.1, M=36.0)),
+    (3072, 512, 192, dict(L=62.6, M=55.0)), (3072, 1024, 64, dict(L=53.8, M=36.0)),
+    (4096, 64, 64, dict(G=8.19, M=41.3)), (4096, 256, 64, dict(G=31.9, L=57.1, M=42.1)),
+    (4096, 256, 96, dict(L=57.8, M=45.1)), (4096, 256, 192, dict(L=58.2, M=85.5)),
+    (4096, 384, 64, dict(G=47.3, L=85.5, M=42.4)), (4096, 512, 64, dict(L=113.8, M=45.1)),
+    (4096, 512, 128, dict(L=115.0, M=86.4)), (4096, 512, 192, dict(L=116.7, M=131.2)),
+    (4096, 1024, 64, dict(L=226.6, M=86.4)), (4096, 256, 256, dict(L=62.0, M=86.4)),
+    (6144, 64, 64, dict(G=30.5, M=68.0)), (6144, 128, 64, dict(G=59.6, M=66.3)),
+    (6144, 256, 64, dict(G=117.4, M=111.5)), (6144, 512, 64, dict(G=235.1, M=221.7)),
+    (8192, 64, 64, dict(G=94.1, M=146.2)), (8192, 128, 64, dict(G=185.4, M=154.2)),
+    (8192, 256, 64, dict(G=367.7, M=260.1)), (8192, 512, 64, dict(G=735.2, M=515.4)),
+]
+BLINDED = [
+    (1024, 512, 192, dict(L=4.72, M=4.27)), (1024, 1024, 64, dict(L=2.48, M=2.84)),
+    (2048, 512, 192, dict(L=21.6, M=20.7)), (2048, 1024, 64, dict(L=12.1, M=13.9)),
+    (2048, 256, 256, dict(L=11.3, M=13.9)), (3072, 256, 96, dict(L=29.2, M=22.4)),
+    (3072, 256, 192, dict(L=34.1, M=42.8)), (3072, 512, 64, dict(L=46.7, M=23.2)),
+    (3072, 1024, 64, dict(L=66.7, M=43.8)), (4096, 192, 64, dict(L=74.8, M=50.4, T=44.6)),
+    (4096, 256, 64, dict(L=75.2, M=50.6, T=44.8)), (4096, 512, 64, dict(L=149.6, M=57.0)),
+    (4096, 256, 192, dict(L=79.5, M=101.2)), (4096, 256, 256, dict(L=85.6, M=107.0)),
+    (4096, 1024, 64, dict(L=298.5, M=107.0)),
+]
+
+DRIVER = r"""
+#include "launch_rule.cpp"
+#include <cstdio>
+namespace pmk { uint64_t table_words_per_slot(int, int, int) { return 1; } }
+using namespace pmk;
+int main() {
+    ClassRun r{};
+    unsigned blinded;
+    r.fill_lanes = 8;
+    while (std::scanf("%u %d %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles) == 6) {
+        const char *f;
+        if (!blinded) f = group_launch(r, 256) ? "G" : mont_launch(r, 256) || !fold_lane(kClassBits[r.cls]).nl ? "M" : "L";
+        else f = 2 * r.ntiles <= 512 && joint_two_lanes(r, 256) ? "T" : joint_mont_launch(r, 256) ? "M" : "L";
+        std::puts(f);
+    }
+}
+"""
+
+
+def shape(blinded, bits, keys, chunks):
+    per = 4 if bits in (3072, 4096) else (2 if bits < 3072 else 4)
+    tiles, parts = -(-chunks // 64), -(-chunks // 16)
+    groups = -(-tiles // per)
+    return f"{blinded} {BITS.index(bits)} {keys * tiles} {keys * parts} {keys * groups} {-(-tiles // groups)}"
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("rule")
+    (d / "driver.cpp").write_text(DRIVER)
+    exe = str(d / "driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{CSRC}", str(d / "driver.cpp"), "-o", exe], check=True)
+    return lambda lines: subprocess.run([exe], input="\n".join(lines), check=True, capture_output=True,
+                                        text=True).stdout.split()
+
+
+@pytest.mark.parametrize("blinded,rows", [(0, PLAIN), (1, BLINDED)])
+def test_pick_is_near_the_fastest_form(rule, blinded, rows):
+    picks = rule([shape(blinded, b, k, c) for b, k, c, _ in rows])
+    assert len(picks) == len(rows)
+    slow = [(b, k, c, p, ms) for (b, k, c, ms), p in zip(rows, picks) if ms.get(p, 1e9) > 1.06 * min(ms.values())]
+    assert not slow
