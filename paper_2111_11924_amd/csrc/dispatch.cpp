@@ -140,7 +140,7 @@ uint64_t table_words(const ClassRun &r_) {
     const uint64_t slot = table_words_per_slot(r.cls, 1, r.win);
     uint64_t need = std::max(r.slots_enc * table_words_per_slot(r.cls, 0, 0), r.slots_dec * slot);
     if (fold_group(kClassBits[r.cls]).nl)
-        need = std::max(need, std::min<uint64_t>(8ull * r.ntiles, group_resident(r.cls)) * group_slot_words(r.cls, r.win));
+        need = std::max(need, std::min<uint64_t>(group_units(r.ntiles), group_resident(r.cls)) * group_slot_words(r.cls, r.win));
     if (mont_launch(r, (uint32_t)device_cus()))
         need = std::max(need, std::min<uint64_t>(2ull * r.ntiles, mont_resident(r.cls)) * slot);
     return need;

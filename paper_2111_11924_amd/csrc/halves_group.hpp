@@ -468,8 +468,14 @@ PMK_DEV uint32_t group_tile(const ClassRun &r, uint32_t first) {
     return first ? uni(r.groups[first]) & 0x3FFFFFFFu : 0u;
 }
 
-// Units u = 8 tile + 4 h + part over the tiles from that of group `first` on;
-// parts without a chunk are skipped.
+// Units over the tiles from that of group `first` on, 32 for eight jobs (tile, h):
+// unit 32 g + 8 i + k is job 8 g + k, one of its four parts of 16 chunks.  A job's
+// parts then run on one die (blocks go to the eight dies by number), which keeps its
+// table in L2 (8192 bits, 64 keys with 64 chunks: 94 ms with the parts on four dies, 67).
+// Which part i is turns with the steps of a block, so that where keys have up to
+// 16 or 32 chunks each, and only part 0 or 0 and 1 are there, every block gets its share (256
+// keys with 16 chunks: 17.8 ms at 3072 bits, 31.9 at 4096 with a fixed part per block,
+// 4.5 and 8.1 here).
 template <int CB, int WV>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(fold_group_waves(CB)))) void halves_group_kernel(
     ClassRun r, uint64_t slot_words, uint32_t first) {
@@ -477,9 +483,12 @@ __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(fold_gr
     uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
     Group<CB, WV> g;
     g.setup(lds);
-    for (uint32_t u = 8 * group_tile(r, first) + blockIdx.x; u < 8 * r.ntiles; u += gridDim.x) {
-        const uint32_t tile = u >> 3;
-        const int h = (int)(u >> 2 & 1), part = (int)(u & 3);
+    const uint32_t t0 = group_tile(r, first), units = group_units(r.ntiles - t0), step = gridDim.x < 32 ? 1 : gridDim.x >> 5;
+    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const uint32_t eight = u >> 5, tile = t0 + 4 * eight + (u >> 1 & 3);
+        if (tile >= r.ntiles) continue;
+        const uint32_t k = eight / step;  // the block's step; parts turn by 0, 2, 1, 3
+        const int h = (int)(u & 1), part = (int)((u >> 3) + ((k & 1) << 1 | (k >> 1 & 1)) & 3);
         if (!uni(r.desc[(size_t)tile * kTile + 16 * part].msg_len)) continue;
         halves_group_unit<CB, WV>(g, r, tile, h, part, tbl);
     }

@@ -67,6 +67,14 @@ def test_few_tiles_per_key_blinded(ctx, bits, keys, chunks, mixed):
     check(ctx, bits, keys, chunks, True, mixed)
 
 
+# numbers over blocks: tiles with one, two and all of their four parts, past one step of
+# every block
+@pytest.mark.parametrize("bits,keys,chunks,mixed", [(1024, 280, 7, 0), (2048, 140, 16, 0), (3072, 70, 20, 0),
+                                                    (4096, 70, 16, 33), (6144, 40, 16, 17), (8192, 40, 17, 0)])
+def test_few_parts_per_key(ctx, bits, keys, chunks, mixed):
+    check(ctx, bits, keys, chunks, False, mixed)
+
+
 # so many keys that Montgomery products are the faster form: one lane per number (1024 to
 # 4096 bits), four lanes (6144, 8192); blinded also two lanes (4096)
 @pytest.mark.parametrize("bits,keys,chunks", [(1024, 520, 65), (3072, 400, 33), (3072, 270, 65), (4096, 330, 49),
