@@ -66,14 +66,16 @@ double joint_lane_ms(int bits, uint32_t nw, uint64_t units, uint64_t room, uint3
     }
 }
 
-// Montgomery products: one lane per number up to 4096 bits, four above.
-double mont_ms(int bits, uint64_t jobs, uint64_t room, uint32_t cus) {
+// Montgomery products: one lane per number up to 4096 bits, four above.  `busy`: blocks
+// of one wave do not land evenly, some SIMDs have two whatever the load (4096 bits in
+// the server's rounds: 77 ms for 900 jobs, 43 alone).
+double mont_ms(int bits, uint64_t jobs, uint64_t room, bool busy, uint32_t cus) {
     const uint64_t cu = cus;
     switch (bits) {
-        case 1024: return rounds_ms(jobs, 12 * cu, room, {1.14, 2.06, 2.92});
-        case 2048: return rounds_ms(jobs, 12 * cu, room, {5.76, 11.3, 16.5});
-        case 3072: return rounds_ms(jobs, 8 * cu, room, {18.8, 36.0});
-        case 4096: return rounds_ms(jobs, 8 * cu, room, {44.7, 85.5});
+        case 1024: return rounds_ms(jobs, 12 * cu, room, {busy ? 2.06 : 1.14, busy ? 2.92 : 2.06, 2.92});
+        case 2048: return rounds_ms(jobs, 12 * cu, room, {busy ? 11.3 : 5.76, busy ? 16.5 : 11.3, 16.5});
+        case 3072: return rounds_ms(jobs, 8 * cu, room, {busy ? 36.0 : 18.8, 36.0});
+        case 4096: return rounds_ms(jobs, 8 * cu, room, {busy ? 85.5 : 44.7, 85.5});
         // 4 waves per job; a partial round after a full one runs beside its last waves
         case 6144:
             if (jobs < 2 * cu) return rounds_ms(jobs, 2 * cu, room / 4, {67.0, 111.5});
@@ -104,34 +106,50 @@ double group_ms(int bits, uint64_t blocks, uint32_t cus) {
         case 3072: return rounds_ms(blocks, 2 * cu, all, {3.65, 4.5});
         case 4096: return rounds_ms(blocks, 2 * cu, all, {6.3, 8.1});
         case 6144: return rounds_ms(blocks, cu, all, {15.2});
-        default: return rounds_ms(blocks, cu, all, {39.2, 46.5});
+        default: return rounds_ms(blocks, cu, all, {34.6, 48.7});
     }
 }
 
 }  // namespace
 
+// The last `groups` groups of the launch's tiles spread over blocks (about as many
+// blocks as groups of its average size have).
+static double group_rest_ms(const ClassRun &r, uint32_t groups, uint32_t cus) {
+    return group_ms(kClassBits[r.cls], 8ull * r.ntiles * groups / r.ngroups, cus);
+}
+
+bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus) {
+    return fold_lane_block(kClassBits[r.cls]) > 2 && r.tail_lanes > 0 && r.fill_lanes > 1 &&
+           group_rest_ms(r, groups, cus) < lane_ms(kClassBits[r.cls], r.group_tiles, 2ull * groups, ~0ull, cus);
+}
+
+// The lane form of a launch, its partial round spread over blocks where that is faster.
+static double lane_launch_ms(const ClassRun &r, uint64_t room, uint32_t cus) {
+    const int bits = kClassBits[r.cls];
+    const uint32_t round = std::max(1u, bits > 3072 ? cus / 2 : cus), rest = r.ngroups % round;  // groups (3072, 4096 bits)
+    room /= r.group_tiles;
+    if (r.group_tiles > 1 && rest && r.ngroups > round && room >= 2 * round && group_rest(r, rest, cus))
+        return lane_ms(bits, r.group_tiles, 2ull * (r.ngroups - rest), room, cus) + group_rest_ms(r, rest, cus);
+    return lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room, cus);
+}
+
 bool mont_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     if (!fold_lane(bits).nl) return false;
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
-    return mont_ms(bits, 2ull * r.ntiles, room, cus) <
-           lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus);
+    return mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus) < lane_launch_ms(r, room, cus);
 }
 
 bool group_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits)) return false;
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
-    double other = mont_ms(bits, 2ull * r.ntiles, room, cus);
-    if (fold_lane(bits).nl)
-        other = std::min(other, lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus));
+    double other = mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus);
+    if (fold_lane(bits).nl) other = std::min(other, lane_launch_ms(r, room, cus));
+    // where most tiles have most of their parts, some block finds one at each of its steps
+    const uint64_t blocks = r.parts > 2 * r.ntiles ? 8ull * r.ntiles : 2ull * r.parts;
     // classes side by side share the chip
-    return group_ms(bits, 2ull * r.parts * std::max(1u, r.share), cus) < other;
-}
-
-bool group_rest(int bits, uint32_t groups, uint32_t cus) {
-    const uint64_t per = fold_lane_block(bits);
-    return group_ms(bits, 8 * per * groups, cus) < lane_ms(bits, (uint32_t)per, 2ull * groups, ~0ull, cus);
+    return group_ms(bits, blocks * std::max(1u, r.share), cus) < other;
 }
 
 bool joint_mont_launch(const ClassRun &r, uint32_t cus) {

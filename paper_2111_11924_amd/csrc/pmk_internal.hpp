@@ -232,6 +232,7 @@ struct ClassRun {
     uint32_t count;            // chunks of this class
     uint32_t parts;            // groups of up to 16 of them under one key
     uint32_t share;            // classes whose launches run beside this one's (0 or 1: none)
+    bool busy;                 // copies or other kernels may run when the launch starts
     uint32_t ntiles;           // key-uniform tiles of this class
     const uint32_t *keys;      // class key table (device), Geom::stride words per key
     const ChunkDesc *desc;     // ntiles * cpt slot descriptors (device)
@@ -456,7 +457,7 @@ bool group_launch(const ClassRun &r, uint32_t cus);
 bool mont_launch(const ClassRun &r, uint32_t cus);
 bool joint_mont_launch(const ClassRun &r, uint32_t cus);
 bool joint_two_lanes(const ClassRun &r, uint32_t cus);
-bool group_rest(int bits, uint32_t groups, uint32_t cus);
+bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus);
 // table words that a class's launches use: plain, and blinded decryption
 uint64_t table_words(const ClassRun &r);
 uint64_t joint_table_words(const ClassRun &r);

@@ -272,6 +272,7 @@ int launch_round(Server *sv, RoundPlan &R, int decrypt, const std::vector<Taken>
         hipError_t e = ensure_class(sv, R, c, tiles);
         if (e != hipSuccess) return (int)e;
         r.ntiles = (uint32_t)tiles;
+        r.busy = true;  // copies of other requests
         r.keys = ctx->d_keys[c];
         r.err = R.pl.d_err;
         r.slot_err = decrypt ? R.slot_err[c] : nullptr;

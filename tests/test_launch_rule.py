@@ -52,6 +52,7 @@ int main() {
     ClassRun r{};
     unsigned blinded;
     r.fill_lanes = 8;
+    r.tail_lanes = 1;
     while (std::scanf("%u %d %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles) == 6) {
         const char *f;
         if (!blinded) f = group_launch(r, 256) ? "G" : mont_launch(r, 256) || !fold_lane(kClassBits[r.cls]).nl ? "M" : "L";
@@ -67,6 +68,12 @@ def shape(blinded, bits, keys, chunks):
     tiles, parts = -(-chunks // 64), -(-chunks // 16)
     groups = -(-tiles // per)
     return f"{blinded} {BITS.index(bits)} {keys * tiles} {keys * parts} {keys * groups} {-(-tiles // groups)}"
+
+
+# groups of mixed sizes, the last ones spread over blocks (L): job tiles, parts, groups of
+# the shape, ms
+MIXED = [(4096, 722, 1240, 140, 4, dict(L=35.5, M=42.7)), (4096, 1044, 1900, 174, 4, dict(L=49.0, M=84.1)),
+         (3072, 722, 1240, 140, 4, dict(L=23.9, M=17.9)), (3072, 1044, 1900, 174, 4, dict(L=25.5, M=37.0))]
 
 
 @pytest.fixture(scope="module")
@@ -86,4 +93,10 @@ def test_pick_is_near_the_fastest_form(rule, blinded, rows):
     picks = rule([shape(blinded, b, k, c) for b, k, c, _ in rows])
     assert len(picks) == len(rows)
     slow = [(b, k, c, p, ms) for (b, k, c, ms), p in zip(rows, picks) if ms.get(p, 1e9) > 1.06 * min(ms.values())]
+    assert not slow
+
+
+def test_partial_round_over_blocks_counts(rule):
+    picks = rule([f"0 {BITS.index(b)} {jt // 2} {parts} {g} {most}" for b, jt, parts, g, most, _ in MIXED])
+    slow = [(row, p) for row, p in zip(MIXED, picks) if row[5].get(p, 1e9) > 1.06 * min(row[5].values())]
     assert not slow
