@@ -118,8 +118,13 @@ static double group_rest_ms(const ClassRun &r, uint32_t groups, uint32_t cus) {
     return group_ms(kClassBits[r.cls], 8ull * r.ntiles * groups / r.ngroups, cus);
 }
 
+// whether the grid limit holds a block of the group form
+static bool group_fits(const ClassRun &r) {
+    return !r.grid_cap || r.grid_cap >= (uint32_t)fold_group_block(kClassBits[r.cls]);
+}
+
 bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus) {
-    return fold_lane_block(kClassBits[r.cls]) > 2 && r.tail_lanes > 0 && r.fill_lanes > 1 &&
+    return fold_lane_block(kClassBits[r.cls]) > 2 && r.tail_lanes > 0 && r.fill_lanes > 1 && group_fits(r) &&
            group_rest_ms(r, groups, cus) < lane_ms(kClassBits[r.cls], r.group_tiles, 2ull * groups, ~0ull, cus);
 }
 
@@ -142,7 +147,7 @@ bool mont_launch(const ClassRun &r, uint32_t cus) {
 
 bool group_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
-    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits)) return false;
+    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits) || !group_fits(r)) return false;
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
     double other = mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus);
     if (fold_lane(bits).nl) other = std::min(other, lane_launch_ms(r, room, cus));

@@ -53,7 +53,8 @@ int main() {
     unsigned blinded;
     r.fill_lanes = 8;
     r.tail_lanes = 1;
-    while (std::scanf("%u %d %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles) == 6) {
+    while (std::scanf("%u %d %u %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles,
+                      &r.grid_cap) == 7) {
         const char *f;
         if (!blinded) f = group_launch(r, 256) ? "G" : mont_launch(r, 256) || !fold_lane(kClassBits[r.cls]).nl ? "M" : "L";
         else f = 2 * r.ntiles <= 512 && joint_two_lanes(r, 256) ? "T" : joint_mont_launch(r, 256) ? "M" : "L";
@@ -63,11 +64,11 @@ int main() {
 """
 
 
-def shape(blinded, bits, keys, chunks):
+def shape(blinded, bits, keys, chunks, cap=0):
     per = 4 if bits in (3072, 4096) else (2 if bits < 3072 else 4)
     tiles, parts = -(-chunks // 64), -(-chunks // 16)
     groups = -(-tiles // per)
-    return f"{blinded} {BITS.index(bits)} {keys * tiles} {keys * parts} {keys * groups} {-(-tiles // groups)}"
+    return f"{blinded} {BITS.index(bits)} {keys * tiles} {keys * parts} {keys * groups} {-(-tiles // groups)} {cap}"
 
 
 # groups of mixed sizes, the last ones spread over blocks (L): job tiles, parts, groups of
@@ -97,6 +98,14 @@ def test_pick_is_near_the_fastest_form(rule, blinded, rows):
 
 
 def test_partial_round_over_blocks_counts(rule):
-    picks = rule([f"0 {BITS.index(b)} {jt // 2} {parts} {g} {most}" for b, jt, parts, g, most, _ in MIXED])
+    picks = rule([f"0 {BITS.index(b)} {jt // 2} {parts} {g} {most} 0" for b, jt, parts, g, most, _ in MIXED])
     slow = [(row, p) for row, p in zip(MIXED, picks) if row[5].get(p, 1e9) > 1.06 * min(row[5].values())]
     assert not slow
+
+
+@pytest.mark.parametrize("bits,waves", [(1024, 1), (2048, 2), (3072, 4), (4096, 4), (6144, 7), (8192, 8)])
+def test_grid_limit_below_a_block(rule, bits, waves):
+    """A limit on the resident waves below a group block's waves leaves one-wave blocks."""
+    caps = range(1, waves + 2)
+    picks = rule([shape(0, bits, 4, 16, cap) for cap in caps])
+    assert [p == "G" for p in picks] == [cap >= waves for cap in caps]
