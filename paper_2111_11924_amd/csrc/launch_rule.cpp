@@ -157,6 +157,16 @@ bool group_launch(const ClassRun &r, uint32_t cus) {
     return group_ms(bits, blocks * std::max(1u, r.share), cus) < other;
 }
 
+bool fills_chip(const ClassRun &r_, uint32_t classes, uint32_t cus) {
+    const int bits = kClassBits[r_.cls];
+    ClassRun r = r_;
+    r.share = classes;
+    if (!fold_group(bits).nl || group_launch(r, cus)) return false;
+    r.share = 1;
+    const uint64_t waves = group_launch(r, cus) ? 2ull * r.parts * fold_group_block(bits) : 2ull * r.ntiles;
+    return waves >= 2 * (uint64_t)cus;
+}
+
 bool joint_mont_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     if (!fold_lane(bits).nl) return false;

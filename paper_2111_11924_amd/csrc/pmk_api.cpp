@@ -578,18 +578,15 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
             return (double)pl->runs[c].ntiles * kClassBits[c] * (2 * s * s + s);
         };
         std::sort(order, order + nl, [&](int x, int y) { return work(x) > work(y); });
-        // Classes too large for the group form beside the others fill the chip by
-        // themselves: they follow one another on `stream`, as pmk_decrypt_plan
-        // launches them, largest first, and the small ones run beside them.  Without
+        // Classes too large for the group form beside the others that hold half of the
+        // SIMDs or more (fills_chip) fill the chip by themselves: they follow one
+        // another on `stream`, as pmk_decrypt_plan launches them, largest first, and the
+        // small ones run beside them.  Without
         // any, or where all together leave SIMDs idle, all run side by side.  25 MiB
         // in four classes: 57.6 ms one after another; on three streams 54 to 70, as
         // 4096-bit blocks, which need whole compute units, are placed before or after
         // the others' (60.4 with Montgomery products).  3 MB: 16.4 and 12.6 ms.
-        auto fills = [&](int c) {
-            ClassRun r = pl->runs[c];
-            r.share = (uint32_t)nl;
-            return fold_group(kClassBits[c]).nl && !group_launch(r, (uint32_t)ctx->num_cus);
-        };
+        auto fills = [&](int c) { return fills_chip(pl->runs[c], (uint32_t)nl, (uint32_t)ctx->num_cus); };
         double load = 0;  // of the SIMDs' waves, one lane per number
         for (int i = 0; i < nl; ++i)
             load += 2.0 * pl->runs[order[i]].ntiles / (4.0 * ctx->num_cus * fold_lane_waves(kClassBits[order[i]]));
@@ -624,6 +621,8 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
             r.share = (uint32_t)nl;
             if (!fold_group(kClassBits[order[i]]).nl) r.fill_lanes = 1;
             r.tail_lanes = 0;
+        } else if (decrypt && lanes > 1) {
+            r.busy = true;  // the small classes beside it
         }
         void *s = decrypt ? stream_of(lane_of(i)) : stream;
         e = timed_launch(pl, decrypt ? PMK_KERNEL_CRT_HALVES : PMK_KERNEL_ENCRYPT, s, [&] {

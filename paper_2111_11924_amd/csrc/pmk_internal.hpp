@@ -458,6 +458,9 @@ bool mont_launch(const ClassRun &r, uint32_t cus);
 bool joint_mont_launch(const ClassRun &r, uint32_t cus);
 bool joint_two_lanes(const ClassRun &r, uint32_t cus);
 bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus);
+// Whether a class, of `classes` that run side by side, is too large for the group form
+// beside the others and holds half of the SIMDs or more by itself.
+bool fills_chip(const ClassRun &r, uint32_t classes, uint32_t cus);
 // table words that a class's launches use: plain, and blinded decryption
 uint64_t table_words(const ClassRun &r);
 uint64_t joint_table_words(const ClassRun &r);

@@ -56,7 +56,8 @@ int main() {
     while (std::scanf("%u %d %u %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles,
                       &r.grid_cap) == 7) {
         const char *f;
-        if (!blinded) f = group_launch(r, 256) ? "G" : mont_launch(r, 256) || !fold_lane(kClassBits[r.cls]).nl ? "M" : "L";
+        if (blinded == 2) f = fills_chip(r, 4, 256) ? "alone" : "beside";
+        else if (!blinded) f = group_launch(r, 256) ? "G" : mont_launch(r, 256) || !fold_lane(kClassBits[r.cls]).nl ? "M" : "L";
         else f = 2 * r.ntiles <= 512 && joint_two_lanes(r, 256) ? "T" : joint_mont_launch(r, 256) ? "M" : "L";
         std::puts(f);
     }
@@ -109,3 +110,11 @@ def test_grid_limit_below_a_block(rule, bits, waves):
     caps = range(1, waves + 2)
     picks = rule([shape(0, bits, 4, 16, cap) for cap in caps])
     assert [p == "G" for p in picks] == [cap >= waves for cap in caps]
+
+
+@pytest.mark.parametrize("bits,keys,chunks,where", [
+    # 200 group blocks of one or two waves leave room beside them on 1,024 SIMDs, 800 do not
+    (1024, 100, 16, "beside"), (2048, 112, 16, "beside"), (1024, 100, 64, "alone"), (1024, 406, 64, "alone"), (2048, 406, 64, "alone"), (3072, 406, 64, "alone"), (4096, 406, 64, "alone"),
+    (4096, 64, 64, "alone")])
+def test_classes_that_fill_the_chip(rule, bits, keys, chunks, where):
+    assert rule([shape(2, bits, keys, chunks)]) == [where]
