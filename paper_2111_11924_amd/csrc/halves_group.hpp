@@ -468,14 +468,15 @@ PMK_DEV uint32_t group_tile(const ClassRun &r, uint32_t first) {
     return first ? uni(r.groups[first]) & 0x3FFFFFFFu : 0u;
 }
 
-// Units over the tiles from that of group `first` on, 32 for eight jobs (tile, h):
-// unit 32 g + 8 i + k is job 8 g + k, one of its four parts of 16 chunks.  A job's
-// parts then run on one die (blocks go to the eight dies by number), which keeps its
-// table in L2 (8192 bits, 64 keys with 64 chunks: 94 ms with the parts on four dies, 67).
-// Which part i is turns with the steps of a block, so that where keys have up to
-// 16 or 32 chunks each, and only part 0 or 0 and 1 are there, every block gets its share (256
-// keys with 16 chunks: 17.8 ms at 3072 bits, 31.9 at 4096 with a fixed part per block,
-// 4.5 and 8.1 here).
+// Jobs (tile, h) over the tiles from that of group `first` on, each in four parts of 16
+// chunks; parts without a chunk are skipped.  The grid takes a quarter of its blocks' number
+// of jobs at a time, the blocks of a part one after another.  A job's parts then run
+// on one die (blocks go to the eight dies by number), which keeps its table in L2
+// (8192 bits, 64 keys with 64 chunks: 94 ms with the parts on four dies, 67), and where
+// keys have up to 16 chunks each, and only part 0 is there, its blocks spread over all
+// compute units.  A block's part turns from step to step, so that every block gets its
+// share of them (256 keys with 16 chunks: 17.8 ms at 3072 bits, 31.9 at 4096 with a
+// fixed part per block, 4.5 and 8.1 here).
 template <int CB, int WV>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(fold_group_waves(CB)))) void halves_group_kernel(
     ClassRun r, uint64_t slot_words, uint32_t first) {
@@ -483,14 +484,15 @@ __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(fold_gr
     uint32_t *tbl = r.table + (size_t)blockIdx.x * slot_words;
     Group<CB, WV> g;
     g.setup(lds);
-    const uint32_t t0 = group_tile(r, first), units = group_units(r.ntiles - t0), step = gridDim.x < 32 ? 1 : gridDim.x >> 5;
-    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const uint32_t eight = u >> 5, tile = t0 + 4 * eight + (u >> 1 & 3);
-        if (tile >= r.ntiles) continue;
-        const uint32_t k = eight / step;  // the block's step; parts turn by 0, 2, 1, 3
-        const int h = (int)(u & 1), part = (int)((u >> 3) + ((k & 1) << 1 | (k >> 1 & 1)) & 3);
-        if (!uni(r.desc[(size_t)tile * kTile + 16 * part].msg_len)) continue;
-        halves_group_unit<CB, WV>(g, r, tile, h, part, tbl);
+    const uint32_t t0 = group_tile(r, first), jobs = 2 * (r.ntiles - t0), some = gridDim.x < 4 ? 1 : gridDim.x / 4;
+    for (uint32_t j0 = 0, k = 0; j0 < jobs; j0 += some, ++k) {  // parts turn by 0, 2, 1, 3
+        const uint32_t left = (jobs - j0 + 7) & ~7u, n = left < some ? left : some;
+        for (uint32_t x = blockIdx.x; x < 4 * n; x += gridDim.x) {
+            const uint32_t jt = j0 + x % n, tile = t0 + (jt >> 1);
+            const int h = (int)(jt & 1), part = (int)(x / n + ((k & 1) << 1 | (k >> 1 & 1)) & 3);
+            if (jt >= jobs || !uni(r.desc[(size_t)tile * kTile + 16 * part].msg_len)) continue;
+            halves_group_unit<CB, WV>(g, r, tile, h, part, tbl);
+        }
     }
 }
 
