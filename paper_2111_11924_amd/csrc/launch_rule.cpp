@@ -182,4 +182,25 @@ bool joint_two_lanes(const ClassRun &r, uint32_t cus) {
                                                         joint_lane_ms(4096, r.group_tiles, units, ~0ull, cus));
 }
 
+std::vector<uint64_t> whole_round_cuts(const uint32_t *key_map, uint64_t nchunks, uint32_t nkeys, uint64_t round,
+                                       uint32_t group) {
+    std::vector<uint64_t> cuts;
+    std::vector<uint32_t> cnt(nkeys, 0);
+    const uint32_t whole = group * kTile;
+    uint64_t tiles = 0, ragged = 0, want = round;
+    for (uint64_t i = 0; i < nchunks; ++i) {
+        uint32_t &n = cnt[key_map[i]];
+        if (n % kTile == 0) ++tiles;
+        if (n % whole == 0) ++ragged;
+        if (++n % whole == 0) --ragged;
+        if (ragged == 0 && tiles == want && i + 1 < nchunks) {
+            cuts.push_back(i + 1);
+            want = 2 * want + round;  // next slice twice as long
+        } else if (tiles > want) {
+            want = (tiles / round + 1) * round;  // no cut there: the next round end
+        }
+    }
+    return cuts;
+}
+
 }  // namespace pmk

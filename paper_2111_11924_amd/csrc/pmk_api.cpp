@@ -1115,37 +1115,18 @@ namespace {
 // offsets relative to the slice), device copies of the whole input and output,
 // and the pipeline's streams and events.
 // Cuts of a decryption into slices that each end on a whole round of CRT
-// work: a plan of one one-lane class whose slices [0, c_1), [c_1, c_2), ...
-// give every key only full tiles and 1, 2, 4, ... rounds of job tiles (one
-// job tile per resident wave) -- so slicing adds no partial round, and the
-// copies of one slice overlap the kernels of its neighbours.  Empty when the
-// key map has no such cuts (then one slice).
+// work (whole_round_cuts): a plan of one one-lane class.  Empty when the key map
+// has no such cuts (then one slice).
 std::vector<uint64_t> round_cuts(const pmk_plan *pl) {
     const pmk_ctx *ctx = pl->ctx;
-    std::vector<uint64_t> cuts;
-    if (pl->nchunks == 0) return cuts;
+    if (pl->nchunks == 0) return {};
     const int c = ctx->keys[pl->key_map[0]].cls;
-    if (lanes_half(kClassBits[c]) != 1) return cuts;
+    if (lanes_half(kClassBits[c]) != 1) return {};
     for (uint64_t i = 0; i < pl->nchunks; ++i)
-        if (ctx->keys[pl->key_map[i]].cls != c) return cuts;
-    const uint64_t tiles_per_round = std::max<uint32_t>(1, wave_slots(c, 1, ctx->num_cus) / 2);
-    std::vector<uint32_t> cnt(ctx->keys.size(), 0);
-    uint64_t tiles = 0, ragged = 0, want = tiles_per_round;
-    for (uint64_t i = 0; i < pl->nchunks; ++i) {
-        uint32_t &n = cnt[pl->key_map[i]];
-        if (n % kTile == 0) {
-            ++tiles;
-            ++ragged;
-        }
-        if (++n % kTile == 0) --ragged;
-        if (ragged == 0 && tiles == want && i + 1 < pl->nchunks) {
-            cuts.push_back(i + 1);
-            want = 2 * want + tiles_per_round;  // next slice twice as long
-        } else if (tiles > want) {
-            want = (tiles / tiles_per_round + 1) * tiles_per_round;  // no cut there: the next round end
-        }
-    }
-    return cuts;
+        if (ctx->keys[pl->key_map[i]].cls != c) return {};
+    return whole_round_cuts(pl->key_map.data(), pl->nchunks, (uint32_t)ctx->keys.size(),
+                            std::max<uint32_t>(1, wave_slots(c, 1, ctx->num_cus) / 2),
+                            fold_lane(kClassBits[c]).nl ? fold_lane_block(kClassBits[c]) : 1);
 }
 
 // Host pipeline of a plan: its chunks cut into slices -- n slices of about

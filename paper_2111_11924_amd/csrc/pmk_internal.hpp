@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <vector>
+
 #if defined(__HIPCC__)
 #define PMK_HD __host__ __device__
 #else
@@ -461,6 +463,13 @@ bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus);
 // Whether a class, of `classes` that run side by side, is too large for the group form
 // beside the others and holds half of the SIMDs or more by itself.
 bool fills_chip(const ClassRun &r, uint32_t classes, uint32_t cus);
+// Cuts of a chunk range into slices [0, c_1), [c_1, c_2), ... that give every key only
+// whole groups of `group` full tiles and 1, 2, 4, ... rounds of `round` tiles: slicing
+// adds no partial round and splits no group (4096 bits, whose rounds need groups of four
+// tiles: 256 keys with 256 chunks each, cut into halves of two tiles per key, took 116
+// ms, uncut 64), and the copies of one slice overlap the kernels of its neighbours.
+std::vector<uint64_t> whole_round_cuts(const uint32_t *key_map, uint64_t nchunks, uint32_t nkeys, uint64_t round,
+                                       uint32_t group);
 // table words that a class's launches use: plain, and blinded decryption
 uint64_t table_words(const ClassRun &r);
 uint64_t joint_table_words(const ClassRun &r);

@@ -46,9 +46,18 @@ BLINDED = [
 DRIVER = r"""
 #include "launch_rule.cpp"
 #include <cstdio>
+#include <cstdlib>
 namespace pmk { uint64_t table_words_per_slot(int, int, int) { return 1; } }
 using namespace pmk;
-int main() {
+int main(int argc, char **argv) {
+    if (argc > 1) {  // keys, chunks per key, tiles of a round, tiles of a group: the cuts
+        const unsigned keys = std::atoi(argv[1]), n = keys * std::atoi(argv[2]);
+        std::vector<uint32_t> km(n);
+        for (unsigned i = 0; i < n; ++i) km[i] = i % keys;
+        for (uint64_t c : whole_round_cuts(km.data(), n, keys, std::atoi(argv[3]), std::atoi(argv[4])))
+            std::printf("%llu\n", (unsigned long long)c);
+        return 0;
+    }
     ClassRun r{};
     unsigned blinded;
     r.fill_lanes = 8;
@@ -86,8 +95,8 @@ def rule(tmp_path_factory):
     (d / "driver.cpp").write_text(DRIVER)
     exe = str(d / "driver")
     subprocess.run(["g++", "-std=c++17", "-O1", f"-I{CSRC}", str(d / "driver.cpp"), "-o", exe], check=True)
-    return lambda lines: subprocess.run([exe], input="\n".join(lines), check=True, capture_output=True,
-                                        text=True).stdout.split()
+    return lambda lines, *args: subprocess.run([exe, *map(str, args)], input="\n".join(lines), check=True,
+                                               capture_output=True, text=True).stdout.split()
 
 
 @pytest.mark.parametrize("blinded,rows", [(0, PLAIN), (1, BLINDED)])
@@ -118,3 +127,12 @@ def test_grid_limit_below_a_block(rule, bits, waves):
     (4096, 64, 64, "alone")])
 def test_classes_that_fill_the_chip(rule, bits, keys, chunks, where):
     assert rule([shape(2, bits, keys, chunks)]) == [where]
+
+
+@pytest.mark.parametrize("keys,chunks,round_,group,cuts", [
+    (256, 256, 512, 4, []),               # a cut after two tiles of each key would split its group of four
+    (256, 512, 512, 4, [256 * 256]),      # 1,024 tiles in whole groups
+    (256, 26 * 64, 1024, 2, [256 * 256, 256 * 256 * 3]),
+    (64, 256, 16, 1, [64 * 64, 64 * 64 * 3])])
+def test_slices_keep_whole_groups(rule, keys, chunks, round_, group, cuts):
+    assert [int(x) for x in rule([], keys, chunks, round_, group)] == cuts
