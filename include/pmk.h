@@ -278,11 +278,12 @@ int pmk_set_grid_limit(pmk_ctx *ctx, uint32_t waves);
  * lanes (pmk_set_lanes); a form with more lanes is kept only if it wins by
  * 1 %.  cache_path (may be NULL): a
  * text file -- a signature line (GPU architecture, compute units, HIP runtime
- * version), then "<class bits> <window> <fill lanes> <tail lanes> <ms>"
+ * version, kernel forms), then "<class bits> <window> <fill lanes> <tail lanes> <ms>"
  * lines.  When it exists and its signature matches this device, its windows
  * and lanes are applied without measuring, unless flags has
- * PMK_AUTOTUNE_FORCE; otherwise the measured choice is written there.  Synchronous; allocates (and frees) its own device buffers; needs a
- * loaded key table (PMK_EINVAL otherwise).
+ * PMK_AUTOTUNE_FORCE; otherwise (also where the file was written for other kernel
+ * forms) the measured choice is written there.  Synchronous; allocates (and frees)
+ * its own device buffers; needs a loaded key table (PMK_EINVAL otherwise).
  */
 enum { PMK_AUTOTUNE_FORCE = 1 };
 int pmk_autotune(pmk_ctx *ctx, const char *cache_path, int flags);

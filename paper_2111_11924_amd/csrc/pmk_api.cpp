@@ -800,12 +800,13 @@ int pmk_set_grid_limit(pmk_ctx *ctx, uint32_t waves) {
 
 namespace {
 
-// identity of the device and runtime an autotuning result belongs to
+// identity of the device, the runtime and the kernel forms (what the tuned values choose
+// between) an autotuning result belongs to
 std::string tune_signature(const pmk_ctx *ctx) {
     int rt = 0;
     (void)hipRuntimeGetVersion(&rt);
     char buf[256];
-    std::snprintf(buf, sizeof buf, "pmk-autotune 2 %s cus=%d hip=%d", ctx->device_name.c_str(), ctx->num_cus, rt);
+    std::snprintf(buf, sizeof buf, "pmk-autotune 2 %s cus=%d hip=%d forms=fold", ctx->device_name.c_str(), ctx->num_cus, rt);
     return buf;
 }
 
@@ -974,13 +975,15 @@ int pmk_autotune(pmk_ctx *ctx, const char *cache_path, int flags) {
             const uint64_t resident = wave_slots(c, 1, ctx->num_cus);  // one-lane waves, 2 per tile
             const uint64_t sizes[2] = {std::max<uint64_t>(1, (uint64_t)ctx->num_cus / 4),
                                        std::max<uint64_t>(1, resident * 2 / 3)};
-            for (int which = 0; which < 2 && rc == PMK_OK; ++which) {
+            // the partial round of a class with a fold form keeps its setting: the launch
+            // rule places it, and 1, 2 and 4 lanes mean the same there
+            for (int which = 0; which < (fold_group(cb).nl ? 1 : 2) && rc == PMK_OK; ++which) {
                 float lbest = 1e30f;
                 int lpick = 1;
                 for (int L : {1, 2, 4, 8}) {
                     if (L == 8 && (which == 1 || !eight_lanes(cb))) continue;  // fill only, where supported
                     // with a group form: one lane, or that form (any other count)
-                    if (fold_group(cb).nl && L != 1 && (which == 1 || L != default_fill_lanes(cb))) continue;
+                    if (fold_group(cb).nl && L != 1 && L != default_fill_lanes(cb)) continue;
                     (void)pmk_set_lanes(ctx, (uint32_t)cb, which == 0 ? L : best_fill, which == 0 ? best_tail : L);
                     float ms = 0.f;
                     rc = tune_batch(ctx, k0, sizes[which], st, 3, &ms);
