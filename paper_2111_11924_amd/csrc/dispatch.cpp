@@ -151,15 +151,18 @@ uint64_t joint_table_words(const ClassRun &r_) {
     r.table_words = 0;
     const uint64_t slot = 2 * table_words_per_slot(r.cls, 1, r.win);  // two odd-power tables
     uint64_t need = r.slots_dec * slot;
+    const Geom g = make_geom(kClassBits[r.cls]);
+    if (eight_lanes(kClassBits[r.cls]) && 4ull * r.ntiles <= 4ull * device_cus())  // small enough for lane groups
+        need = std::max<uint64_t>(need, 2ull * r.ntiles * (2ull << (r.win - 1)) * std::max(g.nla, g.nla8) * kTile);
     if (joint_mont_launch(r, (uint32_t)device_cus()))
         need = std::max(need, std::min<uint64_t>(2ull * r.ntiles, joint_mont_resident(r.cls)) * slot);
     return need;
 }
 
-uint32_t table_units(int cls, uint32_t ntiles) {
-    // fold form: a block's waves even where a group has fewer tiles
-    const int bits = kClassBits[cls];
-    return (fold_lane(bits).nl ? fold_lane_block(bits) : 1) * exp_units(cls, 1, ntiles);
+uint32_t table_units(const ClassRun &r) {
+    // fold form: the waves of a block for the largest group, even where a group has fewer tiles
+    if (fold_lane(kClassBits[r.cls]).nl) return 2 * r.ngroups * r.group_tiles;
+    return exp_units(r.cls, 1, r.ntiles);
 }
 
 uint32_t wave_slots(int cls, int decrypt, int num_cus) {

@@ -31,10 +31,8 @@ int launch_class(const ClassRun &r, uint32_t jt_begin, uint32_t jt_end, hipStrea
     // two odd-power tables (T1 for c*, T2 for c_R), each lane's K limbs
     const uint64_t slot = 2 * (uint64_t)(1u << (r.win - 1)) * K * kTile;
     const uint32_t units = (jt_end - jt_begin) * L;
-    // L / lanes_half lane-group slots fit one slot of the class's own blinded
-    // kernel (2 tables of at least 2^(win-1) entries of nla >= K L limbs)
-    uint32_t grid = persistent_grid(units, r.slots_dec * (uint32_t)(L / lanes_half(CB)), r.grid_cap);
-    grid = std::min(grid, resident_of<CB, L>());
+    const uint64_t room = std::max<uint64_t>(1, r.table_words / slot);
+    uint32_t grid = persistent_grid(units, (uint32_t)std::min<uint64_t>(room, resident_of<CB, L>()), r.grid_cap);
     hipLaunchKernelGGL((halves_lanes_joint_kernel<CB, L>), dim3(grid), dim3(64), 0, s, r, slot, jt_begin * L,
                        jt_end * L);
     return (int)hipGetLastError();

@@ -27,7 +27,7 @@ int launch_joint_fold(const ClassRun &r, hipStream_t s) {
     const uint32_t cus = (uint32_t)device_cus();
     uint32_t waves = per * occ.n[per] * cus;
     if (r.grid_cap && r.grid_cap < waves) waves = r.grid_cap;
-    if (eight_lanes(CB) && 2 * r.ntiles < waves && r.slots_dec >= 4 * r.ntiles) {
+    if (eight_lanes(CB) && 2 * r.ntiles < waves) {
         uint32_t lane_units = 0;
         const int L = lanes_for_launch(r, 2 * r.ntiles, waves, 4u * cus, joint_lanes_resident, &lane_units);
         if (L > 2 || (L == 2 && joint_two_lanes(r, cus))) return launch_joint_lanes(r, L, 0, 2 * r.ntiles, s);

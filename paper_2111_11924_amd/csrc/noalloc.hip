@@ -98,11 +98,18 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
     if (!d_ct || !d_msg || ((uintptr_t)d_ct & 3u) || ((uintptr_t)d_msg & 3u))
         return set_err(ctx, PMK_EINVAL, "buffers must be non-NULL and 4-byte aligned");
     // tiles per class, first tile of each key within its class
-    uint32_t tiles[kNumClasses] = {};
+    uint32_t tiles[kNumClasses] = {}, ngroups[kNumClasses] = {}, parts[kNumClasses] = {}, most[kNumClasses] = {};
     for (uint32_t k = 0; k < nk; ++k) {
         const int c = ctx->keys[k].cls;
+        const uint32_t nt = (ctx->na_count[k] + kTile - 1) / kTile;
         ctx->na_tile[k] = tiles[c];
-        tiles[c] += (ctx->na_count[k] + kTile - 1) / kTile;
+        tiles[c] += nt;
+        if (!nt) continue;
+        // groups of this key's tiles, as tile_groups makes them
+        const uint32_t per = (uint32_t)fold_lane_block(kClassBits[c]), g = (nt + per - 1) / per;
+        ngroups[c] += g;
+        most[c] = std::max(most[c], (nt + g - 1) / g);
+        parts[c] += (ctx->na_count[k] + 15) / 16;
     }
     // scratch layout: error word; per class descriptors and tile keys (this
     // prefix mirrors the pinned host buffer); per class packed words, results,
@@ -141,7 +148,12 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         if (!tiles[c]) continue;
         const uint64_t slot_bytes = table_words_per_slot(c, 1, ctx->win[c]) * 4;
         const uint64_t fit = share / slot_bytes;
-        slots[c] = (uint32_t)std::min<uint64_t>({fit, wave_slots(c, 1, ctx->num_cus), table_units(c, tiles[c])});
+        ClassRun r{};
+        r.cls = c;
+        r.ntiles = tiles[c];
+        r.ngroups = ngroups[c];
+        r.group_tiles = most[c];
+        slots[c] = (uint32_t)std::min<uint64_t>({fit, wave_slots(c, 1, ctx->num_cus), table_units(r)});
         if (!slots[c])
             return set_err(ctx, PMK_ESIZE, "no room left in the static scratch for a %d-bit window table",
                            kClassBits[c]);
@@ -160,7 +172,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
                           d[(uint64_t)ctx->na_tile[k] * kTile + ctx->na_count[k]++] =
                               ChunkDesc{off, ct, ks.slot, (uint32_t)len};
                       });
-    uint32_t ngroups[kNumClasses] = {}, parts[kNumClasses] = {}, most[kNumClasses] = {};
+    std::fill(ngroups, ngroups + kNumClasses, 0u);  // now: groups placed per class
     for (uint32_t k = 0; k < nk; ++k) {
         const uint32_t n = ctx->na_count[k];
         if (!n) continue;
@@ -169,14 +181,11 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         uint32_t *tk = (uint32_t *)(h + off_tk[ks.cls]) + ctx->na_tile[k];
         const uint32_t nt = (n + kTile - 1) / kTile;
         for (uint32_t t = 0; t < nt; ++t) tk[t] = ks.slot;
-        parts[ks.cls] += (n + 15) / 16;
-        // groups of this key's tiles, as tile_groups makes them
         uint32_t *groups = (uint32_t *)(h + off_tk[ks.cls]) + tiles[ks.cls];
         const uint32_t per = (uint32_t)fold_lane_block(kClassBits[ks.cls]);
         for (uint32_t t = 0, g = (nt + per - 1) / per; t < nt; --g) {
             const uint32_t m = (nt - t + g - 1) / g;
             groups[ngroups[ks.cls]++] = (ctx->na_tile[k] + t) | (m - 1) << 30;
-            most[ks.cls] = std::max(most[ks.cls], m);
             t += m;
         }
         for (uint32_t i = n; i < nt * kTile; ++i) d[i] = ChunkDesc{0, 0, ks.slot, 0};  // padding slots

@@ -313,13 +313,13 @@ int pmk_plan_create(pmk_ctx *ctx, const uint32_t *key_map, uint64_t nchunks, uin
         const uint64_t tiles = r.ntiles, cpt = (uint64_t)chunks_per_tile(kClassBits[c]);
         r.keys = ctx->d_keys[c];
         r.slots_enc = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 0, ctx->num_cus), exp_units(c, 0, r.ntiles)));
-        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(c, r.ntiles)));
         r.fold = ctx->d_fold[c];
         // the tiles' keys, then the groups of tiles under one key
         std::vector<uint32_t> &tkp = tkeys[c];
         tkp.reserve(2 * tkp.size());
         r.group_tiles = tile_groups(std::vector<uint32_t>(tkp), r.ntiles, fold_lane_block(kClassBits[c]), tkp);
         r.ngroups = (uint32_t)tkp.size() - r.ntiles;
+        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(r)));
         ChunkDesc *d = nullptr;
         uint32_t *tk = nullptr;
         e = dev_alloc(pl, &d, per[c].size() * sizeof(ChunkDesc));

@@ -439,8 +439,8 @@ uint64_t table_words_per_slot(int cls, int decrypt, int win);
 uint32_t wave_slots(int cls, int decrypt, int num_cus);
 // work units (wavefronts' worth of bignums) of the exponentiation kernels
 uint32_t exp_units(int cls, int decrypt, uint32_t ntiles);
-// table slots (waves) a class's CRT-halves launch over ntiles tiles can use
-uint32_t table_units(int cls, uint32_t ntiles);
+// table slots (waves) that a class's CRT-halves launch can use
+uint32_t table_units(const ClassRun &r);
 // CRT halves of a whole launch with numbers spread over blocks (kgroup.inc): units,
 // table words per block, blocks that are resident, and the launch, which leaves
 // fold results in r.half; launch_halves_group takes the tiles from that of group

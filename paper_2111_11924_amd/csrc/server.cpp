@@ -281,11 +281,11 @@ int launch_round(Server *sv, RoundPlan &R, int decrypt, const std::vector<Taken>
             if (e != hipSuccess) return (int)e;
         }
         r.slots_enc = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 0, ctx->num_cus), exp_units(c, 0, r.ntiles)));
-        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(c, r.ntiles)));
         r.fold = ctx->d_fold[c];
         r.group_tiles = tile_groups(std::vector<uint32_t>(R.h_tkey[c]), r.ntiles, fold_lane_block(kClassBits[c]), R.h_tkey[c]);
         r.groups = R.tkey[c] + tiles;
         r.ngroups = (uint32_t)(R.h_tkey[c].size() - tiles);
+        r.slots_dec = std::max<uint32_t>(1, std::min<uint64_t>(wave_slots(c, 1, ctx->num_cus), table_units(r)));
         if (is_wide_class(c)) units += exp_units(c, 0, r.ntiles);
         e = hipMemcpyAsync(R.desc[c], R.h_desc[c].data(), R.h_desc[c].size() * sizeof(ChunkDesc),
                            hipMemcpyHostToDevice, sv->stream);

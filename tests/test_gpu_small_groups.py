@@ -114,3 +114,35 @@ def test_montgomery_form_edges(ctx, bits, keys):
         want[i] = np.frombuffer((0 if v >= key.n else pow(v, key.d, key.n)).to_bytes(kb, "big"), np.uint8)
     np.testing.assert_array_equal(got, want)
     plan.close()
+
+
+def test_blinded_tables_of_single_tiles(ctx):
+    """124 keys with two chunks each: the window tables of blinded decryption hold two odd-power
+    tables of 2^4 numbers of 40 limbs for each of the 248 waves, 81 MB, not twice that."""
+    import torch
+
+    keys, per = 124, 2
+    ctx.load_keys(keys_of(2048, keys))
+    win = ctx.window(2048)
+
+    def run(n):
+        km = np.repeat(np.arange(n, dtype=np.uint32), per)
+        msg = inputs.make_message(len(km) * 252, n)
+        r = inputs.make_message(len(km) * 256, 3).reshape(len(km), 256).copy()
+        r[:, 0] = 0
+        plan = ctx.plan(km, len(msg))
+        args = plan.encrypt_blinded(torch.from_numpy(msg).cuda(), torch.from_numpy(r.reshape(-1)).cuda())
+        before = torch.cuda.mem_get_info()[0]
+        out = plan.decrypt_blinded(*args)
+        assert plan.check() == binding.PMK_OK
+        used = before - torch.cuda.mem_get_info()[0]
+        np.testing.assert_array_equal(out[: len(msg)].cpu().numpy(), msg)
+        plan.close()
+        return used
+
+    ctx.set_window(2048, 5)
+    try:
+        run(2)  # what the first launch of these kernels makes once
+        assert run(keys) <= 124 * 2 * 2 * 16 * 40 * 64 * 4 + (8 << 20)
+    finally:
+        ctx.set_window(2048, win)
