@@ -355,11 +355,11 @@ int pmk_decrypt_host(pmk_plan *plan, const uint8_t *ct, uint8_t *msg, uint32_t s
  * with the same arguments, results and errors, but calling no hipMalloc,
  * hipFree or other allocating routine.  Every device buffer its kernels use
  * (chunk descriptors, packed words, CRT half results, window tables, the
- * error word) lives in one fixed device array of 64 MiB that the library
+ * error word) lives in one fixed device array of 66 MiB that the library
  * holds on each GPU it runs on until the process ends; the host-side planning
  * uses buffers made at pmk_create / pmk_keys_load.  Limits: at most 65,536
  * chunks, and the chunk data plus at least one window table per size class
- * must fit the 64 MiB (PMK_ESIZE, before anything is launched, otherwise);
+ * must fit 64 MiB of it (PMK_ESIZE, before anything is launched, otherwise);
  * fewer table slots than pmk_decrypt's may run the exponentiation in more
  * rounds.  d_ct / d_msg are device memory, key_map host memory.  Synchronous
  * on `stream`.  Every call on one GPU, from any context or thread, shares that

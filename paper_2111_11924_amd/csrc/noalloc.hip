@@ -117,6 +117,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
     uint64_t off_desc[kNumClasses] = {}, off_tk[kNumClasses] = {}, off_x[kNumClasses] = {}, off_y[kNumClasses] = {},
              off_h[kNumClasses] = {}, off_t[kNumClasses] = {};
     uint64_t o = kAlign;  // [0, 4): the error word
+    uint64_t data = kAlign;  // counted against the limit: one tile key per tile, halves of nlh limbs
     int present = 0;
     for (int c = 0; c < kNumClasses; ++c) {
         if (!tiles[c]) continue;
@@ -136,10 +137,12 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
         o += align_up((uint64_t)tiles[c] * g.S * kTile * 4);
         off_h[c] = o;
         o += align_up((uint64_t)tiles[c] * 2 * half_stride(kClassBits[c]) * kTile * 4);
+        data += align_up((uint64_t)tiles[c] * kTile * sizeof(ChunkDesc)) + align_up((uint64_t)tiles[c] * sizeof(uint32_t)) +
+                2 * align_up((uint64_t)tiles[c] * g.S * kTile * 4) + align_up((uint64_t)tiles[c] * 2 * g.nlh * kTile * 4);
     }
-    if (prefix > ctx->na_host_bytes || o >= kNoAllocScratchBytes)
+    if (prefix > ctx->na_host_bytes || data >= kNoAllocDataBytes || o >= kNoAllocScratchBytes)
         return set_err(ctx, PMK_ESIZE, "the chunks need %llu bytes of scratch, the static scratch holds %llu",
-                       (unsigned long long)o, (unsigned long long)kNoAllocScratchBytes);
+                       (unsigned long long)data, (unsigned long long)kNoAllocDataBytes);
     // window tables: what is left, shared evenly by the classes present; each
     // class gets at most its occupancy and its unit count in wave slots
     const uint64_t share = (kNoAllocScratchBytes - o) / (uint64_t)present;
@@ -147,7 +150,7 @@ int pmk_decrypt_noalloc(pmk_ctx *ctx, const uint8_t *d_ct, uint64_t ct_len, cons
     for (int c = 0; c < kNumClasses; ++c) {
         if (!tiles[c]) continue;
         const uint64_t slot_bytes = table_words_per_slot(c, 1, ctx->win[c]) * 4;
-        const uint64_t fit = share / slot_bytes;
+        const uint64_t fit = (kNoAllocDataBytes - data) / (uint64_t)present < slot_bytes ? 0 : share / slot_bytes;
         ClassRun r{};
         r.cls = c;
         r.ntiles = tiles[c];

@@ -13,9 +13,11 @@
 
 namespace pmk {
 struct Server;
-// pmk_decrypt_noalloc: size of the fixed device array holding all its scratch
-// (one per GPU, for the life of the process), and its chunk limit
-constexpr uint64_t kNoAllocScratchBytes = 64ull << 20;
+// pmk_decrypt_noalloc: the chunk data that it takes, size of the fixed device array
+// holding all its scratch (one per GPU, for the life of the process; 2 MiB more, for the
+// fold results' additional limbs and the groups of tiles), and its chunk limit
+constexpr uint64_t kNoAllocDataBytes = 64ull << 20;
+constexpr uint64_t kNoAllocScratchBytes = kNoAllocDataBytes + (2ull << 20);
 constexpr uint64_t kNoAllocMaxChunks = 65536;
 }
 using pmk::ClassRun;
