@@ -1,10 +1,13 @@
 // Tables of the fold forms (fold.hpp), written once per key table.
 //
-// W_i = 2^(F + pos_i) mod m, one lane per i, by one Montgomery product each
+// W_i = 2^(F + pos_i) mod m, one lane per i, by one Montgomery reduction each
 // from the key record's constants: with R = 2^(lbh nlh) and e = F + pos_i -
 // lbh nlh, MM(R^2, 2^e) = 2^(F + pos_i) (MM(R^3, 2^(e - lbh nlh)) where 2^e does not
-// lie below R).  Rolled loops: the setup of a whole key table takes less time
-// than its upload.
+// lie below R).  One block per (key, prime, form), one round of lanes.
+//
+// Bound by the latency of its sums in scratch memory: each pass over them takes eight
+// rows of the product.  16 8192-bit keys: 29.1 ms with a row per pass and the columns in
+// five rounds, 2.8 here; 128 4096-bit keys 10.3 and 1.8.
 #include "fold.hpp"
 #include "mont.hpp"
 
@@ -12,8 +15,7 @@ namespace pmk {
 
 namespace {
 
-constexpr int kMaxHalf = 152;   // limbs of the largest CRT half
-constexpr int kSetupBlock = 128;
+constexpr int kRows = 8;  // rows of a product per pass over its sums
 
 struct SetupArgs {
     const uint32_t *keys;  // key records
@@ -21,33 +23,55 @@ struct SetupArgs {
     uint32_t size;
 };
 
-// r = a b R^-1 mod n, canonical; nl limbs of lb bits, a b < R n
-__device__ void mm(uint32_t *r, const uint32_t *a, const uint32_t *b, const uint32_t *n, uint32_t n0, int nl, int lb) {
-    const uint32_t mask = (1u << lb) - 1u;
-    uint64_t t[kMaxHalf];
-    for (int j = 0; j < nl; ++j) t[j] = 0;
-    for (int i = 0; i < nl; ++i) {
-        const uint32_t bi = b[i];
-        uint64_t c = t[0] + (uint64_t)a[0] * bi;
-        const uint32_t m = ((uint32_t)c * n0) & mask;
-        c = (c + (uint64_t)m * n[0]) >> lb;
-        for (int j = 1; j < nl; ++j) t[j - 1] = t[j] + (uint64_t)a[j] * bi + (uint64_t)m * n[j];
-        t[nl - 1] = 0;
-        t[0] += c;
+// t += sum_r x[r] 2^(LB r) times the NL limbs of n, from limb `from` of t on; limbs
+// below `skip` of the product are left out
+template <int NL>
+__device__ void add_rows(uint64_t *t, const uint32_t (&x)[kRows], const uint32_t *n, int skip) {
+    uint32_t w[kRows] = {};  // n's limbs j, j - 1, ...
+    for (int j = 0; j < NL + kRows - 1; ++j) {
+#pragma unroll
+        for (int r = kRows - 1; r > 0; --r) w[r] = w[r - 1];
+        w[0] = j < NL ? n[j] : 0u;
+        if (j < skip) continue;
+        uint64_t s = t[j];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) s += (uint64_t)x[r] * w[r];
+        t[j] = s;
     }
+}
+
+// r = t R^-1 mod n, canonical (R = 2^(LB NL), t below R n, 2 NL + kRows limbs, overwritten)
+template <int NL, int LB>
+__device__ void redc(uint32_t *r, uint64_t *t, const uint32_t *n, uint32_t n0) {
+    constexpr uint32_t MASK = (1u << LB) - 1u;
     uint64_t c = 0;
-    for (int j = 0; j < nl; ++j) {
-        c += t[j];
-        r[j] = (uint32_t)c & mask;
-        c >>= lb;
+    for (int i = 0; i < NL; i += kRows) {
+        const int rows = NL - i < kRows ? NL - i : kRows;
+        uint32_t m[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            m[k] = 0;
+            if (k >= rows) continue;
+            uint64_t s = t[i + k] + c;
+#pragma unroll
+            for (int l = 0; l < k; ++l) s += (uint64_t)m[l] * n[k - l];
+            m[k] = ((uint32_t)s * n0) & MASK;
+            c = (s + (uint64_t)m[k] * n[0]) >> LB;
+        }
+        add_rows<NL>(t + i, m, n, rows);
+    }
+    for (int j = 0; j < NL; ++j) {
+        c += t[NL + j];
+        r[j] = (uint32_t)c & MASK;
+        c >>= LB;
     }
     // below 2 n: subtract n unless that borrows
     int32_t bw = 0;
-    for (int j = 0; j < nl; ++j) bw = ((int32_t)r[j] - (int32_t)n[j] + bw) >> 31;
+    for (int j = 0; j < NL; ++j) bw = ((int32_t)r[j] - (int32_t)n[j] + bw) >> 31;
     if (bw) return;
-    for (int j = 0; j < nl; ++j) {
+    for (int j = 0; j < NL; ++j) {
         const int32_t v = (int32_t)r[j] - (int32_t)n[j] + bw;
-        r[j] = (uint32_t)v & mask;
+        r[j] = (uint32_t)v & MASK;
         bw = v >> 31;
     }
 }
@@ -59,97 +83,108 @@ __device__ uint32_t bits_of(const uint32_t *x, int nl, int lb, int at, int len) 
     return (uint32_t)((lo | hi << lb) >> sh) & ((1u << len) - 1u);
 }
 
-// One block per (key, prime): the columns of W over the lanes, and the start
-// values of the rows: their biases plus the digits of -(sum of the biases) mod m.
-template <int CB>
-__global__ __launch_bounds__(kSetupBlock) void fold_setup_kernel(SetupArgs a) {
+constexpr int setup_threads(FoldForm f) { return (4 * f.nl + 2 + 63) / 64 * 64; }
+
+// One block per (key, prime) and form: a column of W per lane; two lanes more sum
+// the rows' biases mod m.  The rows' start values are their biases plus the digits of
+// minus that sum mod m.
+template <int CB, bool LANE>
+__global__ __launch_bounds__(setup_threads(LANE ? fold_lane(CB) : fold_group(CB))) void fold_setup_kernel(SetupArgs a) {
     constexpr Geom G = make_geom(CB);
     constexpr int NLH = G.nlh, LBH = G.lbh, RB = NLH * LBH;
-    constexpr FoldTable T = fold_table(CB);
+    constexpr uint32_t MASK = (1u << LBH) - 1u;
+    constexpr FoldForm f = LANE ? fold_lane(CB) : fold_group(CB);
+    constexpr int P = CB / 2, F = f.lb * f.nl, COLS = 4 * f.nl;
+    static_assert(F >= P + 17 && F >= RB && F + f.lb * f.nl < 3 * RB, "fold position");
+    static_assert(COLS % 64 < 62, "both lanes that sum the biases are of one wave");
+    __shared__ uint32_t sums[2][NLH];
     const uint32_t *hr = a.keys + (size_t)(blockIdx.x >> 1) * G.stride + G.off_half[0] + (blockIdx.x & 1) * G.h_size;
     const uint32_t *n = hr + G.h_m;
     const uint32_t n0 = hr[G.h_m0];
-    uint8_t *out = a.out + (size_t)blockIdx.x * a.size;
-    constexpr int P = CB / 2;
-    auto form = [&](auto f_, bool loose, uint8_t *tab, auto element) {
-        constexpr FoldForm f = decltype(f_)::value();
-        constexpr int F = f.lb * f.nl;
-        static_assert(F >= P + 17 && F >= RB && F + f.lb * f.nl < 3 * RB, "fold position");
-        uint32_t x[NLH], b[NLH];
-        for (int i = threadIdx.x; i < 4 * f.nl; i += kSetupBlock) {
-            int e = F + f.lb * (i / 4) + 8 * (i % 4) - RB;
-            const uint32_t *c = hr + (e < RB ? G.h_rr : G.h_rrr);
-            if (e >= RB) e -= RB;
-            for (int j = 0; j < NLH; ++j) b[j] = j == e / LBH ? 1u << (e % LBH) : 0u;
-            mm(x, c, b, n, n0, NLH, LBH);
-            for (int k = 0; k < f.nl; ++k) {
-                const uint32_t d = (bits_of(x, NLH, LBH, f.lb * k, f.lb) + kDigitBias) ^ kDigitBias;
-                for (int j = 0; j < 4; ++j) tab[element(4 * k + j, i)] = (uint8_t)(d >> (8 * j));
-            }
+    uint8_t *tab = a.out + (size_t)blockIdx.x * a.size + (LANE ? fold_table(CB).lane : fold_table(CB).group);
+    auto element = [](int row, int col) {
+        if constexpr (LANE) return FoldShape<f.nl, f.lb>::element(row, col);
+        // row tile row / 16, K step col / 64: 16 bytes of lane 16 (col / 16 % 4) + row % 16
+        else
+            return 16 * f.nl +
+                   ((row / 16 * fold_group_steps(CB) + col / 64) * 64 + col / 16 % 4 * 16 + row % 16) * 16 + col % 16;
+    };
+    uint64_t t[2 * NLH + kRows];
+    for (int j = 0; j < 2 * NLH + kRows; ++j) t[j] = 0;
+    uint32_t x[NLH];
+    const int i = threadIdx.x;
+    if (i < COLS) {
+        int e = F + f.lb * (i / 4) + 8 * (i % 4) - RB;
+        const uint32_t *c = hr + (e < RB ? G.h_rr : G.h_rrr);
+        if (e >= RB) e -= RB;
+        const int q = e / LBH, sh = e % LBH;
+        uint32_t below = 0;  // c 2^e
+        for (int j = 0; j < NLH; ++j) {
+            const uint32_t v = c[j];
+            t[q + j] = ((uint64_t)v << sh | below) & MASK;
+            below = (uint32_t)((uint64_t)v << sh >> LBH);
         }
-        if (threadIdx.x) return;
-        // sum of the biases, lo + R hi
+        t[q + NLH] = below;
+        redc<NLH, LBH>(x, t, n, n0);
+        for (int k = 0; k < f.nl; ++k) {
+            const uint32_t d = (bits_of(x, NLH, LBH, f.lb * k, f.lb) + kDigitBias) ^ kDigitBias;
+            for (int j = 0; j < 4; ++j) tab[element(4 * k + j, i)] = (uint8_t)(d >> (8 * j));
+        }
+    } else if (i < COLS + 2) {
+        // sum of the biases lo + R hi: MM(lo, R) or MM(hi, R^2)
         uint64_t z[2 * NLH];
         for (int j = 0; j < 2 * NLH; ++j) z[j] = 0;
         for (int k = 0; k < f.nl; ++k)
             for (int j = 0; j < 4; ++j) {
                 const int at = f.lb * k + 8 * j;
-                z[at / LBH] += (uint64_t)fold_bias(f, P, k, j, loose) << (at % LBH);
+                z[at / LBH] += (uint64_t)fold_bias(f, P, k, j, !LANE) << (at % LBH);
             }
         uint64_t c = 0;
         for (int j = 0; j < 2 * NLH; ++j) {
             c += z[j];
-            z[j] = c & ((1u << LBH) - 1u);
+            z[j] = c & MASK;
             c >>= LBH;
         }
-        uint32_t y[NLH];
-        for (int j = 0; j < NLH; ++j) b[j] = (uint32_t)z[j];
-        mm(x, hr + G.h_rr, b, n, n0, NLH, LBH);
-        for (int j = 0; j < NLH; ++j) b[j] = (uint32_t)z[NLH + j];
-        mm(y, hr + G.h_rrr, b, n, n0, NLH, LBH);
-        c = 0;
-        for (int j = 0; j < NLH; ++j) {
-            c += (uint64_t)x[j] + y[j];
-            x[j] = (uint32_t)c & ((1u << LBH) - 1u);
-            c >>= LBH;
-            b[j] = j == 0;
+        const int hi = i - COLS;
+        for (int j = 0; j < NLH; j += kRows) {
+            uint32_t rows[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) rows[r] = j + r < NLH ? (uint32_t)z[hi * NLH + j + r] : 0u;
+            add_rows<NLH>(t + j, rows, hr + (hi ? G.h_rr : G.h_one), 0);
         }
-        mm(y, x, b, n, n0, NLH, LBH);  // the sum mod m
-        int32_t bw = 0;
-        for (int j = 0; j < NLH; ++j) {  // m - that
-            const int32_t v = (int32_t)n[j] - (int32_t)y[j] + bw;
-            x[j] = (uint32_t)v & ((1u << LBH) - 1u);
-            bw = v >> 31;
-        }
-        uint32_t *init = (uint32_t *)tab;
-        for (int k = 0; k < f.nl; ++k) {
-            const uint32_t d = bits_of(x, NLH, LBH, f.lb * k, f.lb);
-            for (int j = 0; j < 4; ++j)
-                init[4 * k + j] = fold_bias(f, P, k, j, loose) + (j < 3 ? (d >> (8 * j)) & 255u : d >> 24);
-        }
-    };
-    if constexpr (fold_lane(CB).nl) {
-        struct Lane {
-            static constexpr FoldForm value() { return fold_lane(CB); }
-        };
-        using S = FoldShape<fold_lane(CB).nl, fold_lane(CB).lb>;
-        form(Lane{}, false, out + T.lane, [](int row, int col) { return S::element(row, col); });
+        redc<NLH, LBH>(x, t, n, n0);
+        for (int j = 0; j < NLH; ++j) sums[hi][j] = x[j];
     }
-    if constexpr (fold_group(CB).nl) {
-        struct Group {
-            static constexpr FoldForm value() { return fold_group(CB); }
-        };
-        // row tile row / 16, K step col / 64: 16 bytes of lane 16 (col / 16 % 4) + row % 16
-        form(Group{}, true, out + T.group, [](int row, int col) {
-            return 16 * fold_group(CB).nl +
-                   ((row / 16 * fold_group_steps(CB) + col / 64) * 64 + col / 16 % 4 * 16 + row % 16) * 16 + col % 16;
-        });
+    __syncthreads();
+    if (i) return;
+    // minus the sum: m - lo - hi, plus m where that is negative
+    int32_t bw = 0;
+    for (int j = 0; j < NLH; ++j) {
+        const int32_t v = (int32_t)n[j] - (int32_t)sums[0][j] - (int32_t)sums[1][j] + bw;
+        x[j] = (uint32_t)v & MASK;
+        bw = v >> LBH;
+    }
+    if (bw < 0) {
+        uint32_t cy = 0;
+        for (int j = 0; j < NLH; ++j) {
+            const uint32_t v = x[j] + n[j] + cy;
+            x[j] = v & MASK;
+            cy = v >> LBH;
+        }
+    }
+    uint32_t *init = (uint32_t *)tab;
+    for (int k = 0; k < f.nl; ++k) {
+        const uint32_t d = bits_of(x, NLH, LBH, f.lb * k, f.lb);
+        for (int j = 0; j < 4; ++j)
+            init[4 * k + j] = fold_bias(f, P, k, j, !LANE) + (j < 3 ? (d >> (8 * j)) & 255u : d >> 24);
     }
 }
 
 template <int CB>
 int setup(const SetupArgs &a, uint32_t count, hipStream_t s) {
-    hipLaunchKernelGGL(fold_setup_kernel<CB>, dim3(2 * count), dim3(kSetupBlock), 0, s, a);
+    if constexpr (fold_lane(CB).nl != 0)
+        hipLaunchKernelGGL((fold_setup_kernel<CB, true>), dim3(2 * count), dim3(setup_threads(fold_lane(CB))), 0, s, a);
+    hipLaunchKernelGGL((fold_setup_kernel<CB, false>), dim3(2 * count), dim3(setup_threads(fold_group(CB))), 0, s, a);
     return (int)hipGetLastError();
 }
 
