@@ -141,13 +141,14 @@ static double lane_launch_ms(const ClassRun &r, uint64_t room, uint32_t cus) {
 bool mont_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     if (!fold_lane(bits).nl) return false;
+    if (!r.fold) return true;
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
     return mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus) < lane_launch_ms(r, room, cus);
 }
 
 bool group_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
-    if (!fold_group(bits).nl || r.fill_lanes <= lanes_half(bits) || !group_fits(r)) return false;
+    if (!fold_group(bits).nl || !r.fold || r.fill_lanes <= lanes_half(bits) || !group_fits(r)) return false;
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
     double other = mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus);
     if (fold_lane(bits).nl) other = std::min(other, lane_launch_ms(r, room, cus));
@@ -170,6 +171,7 @@ bool fills_chip(const ClassRun &r_, uint32_t classes, uint32_t cus) {
 bool joint_mont_launch(const ClassRun &r, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     if (!fold_lane(bits).nl) return false;
+    if (!r.fold) return true;
     const uint64_t room = room_of(r, 2 * table_words_per_slot(r.cls, 1, r.win));
     return joint_mont_ms(bits, 2ull * r.ntiles, room, cus) <
            joint_lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room / r.group_tiles, cus);

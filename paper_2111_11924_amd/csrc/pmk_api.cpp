@@ -213,10 +213,17 @@ int pmk_keys_load(pmk_ctx *ctx, const pmk_key *keys, uint32_t nkeys) {
         const size_t bytes = host[c].size() * sizeof(uint32_t);
         e = hipMalloc(&fresh[c], bytes);
         if (e == hipSuccess) e = hipMemcpy(fresh[c], host[c].data(), bytes, hipMemcpyHostToDevice);
-        const uint64_t fb = fold_bytes_per_key(c) * counts[c];
-        if (e != hipSuccess || !fb) continue;
-        e = hipMalloc(&fold[c], fb);
-        if (e == hipSuccess) e = hipMemset(fold[c], 0, fb);
+    }
+    // fold tables, where they fit: 15 to 57 times the records' size
+    for (int c = 0; c < kNumClasses && e == hipSuccess; ++c) {
+        const uint64_t fb = counts[c] ? fold_bytes_per_key(c) * counts[c] : 0;
+        if (!fb) continue;
+        if (hipMalloc(&fold[c], fb) != hipSuccess) {
+            (void)hipGetLastError();  // a class without them decrypts by Montgomery products
+            fold[c] = nullptr;
+            continue;
+        }
+        e = hipMemset(fold[c], 0, fb);
         if (e == hipSuccess) e = (hipError_t)launch_fold_setup(c, fresh[c], counts[c], fold[c], nullptr);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);

@@ -242,7 +242,8 @@ struct ClassRun {
     const uint32_t *groups;    // fold form: ngroups groups of tiles under one key, the first tile and
     uint32_t ngroups;          // the tiles after it in bits 30 and 31 (device);
     uint32_t group_tiles;      // tiles of the largest
-    const uint8_t *fold;       // fold tables of the class's keys (two primes each, fold_table)
+    const uint8_t *fold;       // fold tables of the class's keys (two primes each, fold_table); nullptr:
+                               // they did not fit, Montgomery forms only
     uint32_t *x32;             // [tile][word < S][chunk < cpt]: packed input words
     uint32_t *y32;             // same shape: result words before unpacking
     uint32_t *half;            // [tile][p, q][limb < half_stride][chunk < cpt]: CRT half results

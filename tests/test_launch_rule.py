@@ -62,6 +62,7 @@ int main(int argc, char **argv) {
     unsigned blinded;
     r.fill_lanes = 8;
     r.tail_lanes = 1;
+    r.fold = std::getenv("NO_FOLD") ? nullptr : (const uint8_t *)&blinded;
     while (std::scanf("%u %d %u %u %u %u %u", &blinded, &r.cls, &r.ntiles, &r.parts, &r.ngroups, &r.group_tiles,
                       &r.grid_cap) == 7) {
         const char *f;
@@ -136,3 +137,12 @@ def test_classes_that_fill_the_chip(rule, bits, keys, chunks, where):
     (64, 256, 16, 1, [64 * 64, 64 * 64 * 3])])
 def test_slices_keep_whole_groups(rule, keys, chunks, round_, group, cuts):
     assert [int(x) for x in rule([], keys, chunks, round_, group)] == cuts
+
+
+@pytest.mark.parametrize("bits", [1024, 2048, 3072, 4096, 6144, 8192])
+@pytest.mark.parametrize("keys,chunks", [(1, 7), (64, 64), (256, 256)])
+def test_without_fold_tables(rule, monkeypatch, bits, keys, chunks):
+    monkeypatch.setenv("NO_FOLD", "1")
+    assert rule([shape(0, bits, keys, chunks)]) == ["M"]
+    if bits <= 4096:
+        assert rule([shape(1, bits, keys, chunks)]) in (["M"], ["T"])
