@@ -146,3 +146,40 @@ def test_blinded_tables_of_single_tiles(ctx):
         assert run(keys) <= 124 * 2 * 2 * 16 * 40 * 64 * 4 + (8 << 20)
     finally:
         ctx.set_window(2048, win)
+
+
+# past full rounds of the lane form, the last groups in each of the forms that take them,
+# plain and batched
+@pytest.mark.parametrize("bits,keys,chunks,mixed", [(1024, 40, 2560, 70), (2048, 36, 1920, 70), (3072, 70, 1024, 70),
+                                                    (4096, 66, 512, 70)])
+def test_partial_rounds(ctx, bits, keys, chunks, mixed):
+    check(ctx, bits, keys, chunks, False, mixed)
+
+
+@pytest.mark.parametrize("bits,keys,chunks,mixed", [(1024, 40, 2560, 70), (2048, 36, 1920, 70)])
+def test_partial_rounds_blinded(ctx, bits, keys, chunks, mixed):
+    check(ctx, bits, keys, chunks, True, mixed)
+
+
+@pytest.mark.parametrize("bits,lanes", [(2048, 1), (2048, 8), (3072, 1), (3072, 8), (4096, 1), (4096, 8), (6144, 4),
+                                        (6144, 8), (8192, 4), (8192, 8)])
+def test_edges_under_different_keys(ctx, bits, lanes):
+    """Tiles, groups and parts around their edges, each key another, so that a wrong key or
+    fold table shows."""
+    import torch
+
+    counts = [1, 15, 17, 63, 64, 65, 129, 257] if bits <= 4096 else [1, 15, 17, 65]
+    ctx.load_keys(keys_of(bits, len(counts)))
+    km = np.repeat(np.arange(len(counts), dtype=np.uint32), counts)[::-1].copy()
+    msg = inputs.make_message(len(km) * (bits // 8 - 4) - 7, bits + lanes)
+    old = ctx.lanes(bits)
+    ctx.set_lanes(bits, lanes, old[1])
+    try:
+        plan = ctx.plan(km, len(msg))
+        ct = plan.encrypt(torch.from_numpy(msg).cuda())
+        for out in (plan.decrypt(ct), plan.decrypt(ct, batch=True)):
+            assert plan.check() == binding.PMK_OK
+            np.testing.assert_array_equal(out[: len(msg)].cpu().numpy(), msg)
+        plan.close()
+    finally:
+        ctx.set_lanes(bits, *old)
