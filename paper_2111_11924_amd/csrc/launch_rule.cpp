@@ -27,10 +27,11 @@ uint64_t room_of(const ClassRun &r, uint64_t slot) {
     return r.grid_cap ? std::min<uint64_t>(room, r.grid_cap) : room;
 }
 
-// Fold form in one lane, units of nw waves (tiles of a group, modulo one prime).  A
-// group's table takes LDS whatever its tiles: three 3072-bit blocks or one
-// 4096-bit block fit a compute unit, so that small groups leave SIMDs idle there.
-double lane_ms(int bits, uint32_t nw, uint64_t units, uint64_t room, uint32_t cus) {
+// Fold form in one lane: units of up to nw waves (tiles of a group, modulo one prime),
+// `tiles` of them on average.  A group's table takes LDS whatever its tiles: three 3072-bit
+// blocks or one 4096-bit block fit a compute unit, so that small groups leave SIMDs idle
+// there.
+double lane_ms(int bits, uint32_t nw, double tiles, uint64_t units, uint64_t room, uint32_t cus) {
     const uint64_t cu = cus;
     switch (bits) {
         case 1024:
@@ -39,11 +40,14 @@ double lane_ms(int bits, uint32_t nw, uint64_t units, uint64_t room, uint32_t cu
         case 2048:
             if (nw == 1) return rounds_ms(units, 4 * cu, room, {4.4});
             return rounds_ms(units, 4 * cu, room, {4.4, 8.1});
-        case 3072:
+        case 3072: {
             if (nw == 1) return rounds_ms(units, 3 * cu, room, {14.3, 14.3, 15.8});
-            if (nw == 2) return rounds_ms(units, 2 * cu, room, {15.0, 24.4});
-            if (nw == 3) return rounds_ms(units, 2 * cu, room, {16.0, 29.5});
-            return rounds_ms(units, 2 * cu, room, {17.9, 32.0});
+            // one block per compute unit; two, at first on a few of them
+            const double one = 15.2 + 2.7 * std::max(0., tiles - 3),
+                         two = 24.4 + 5.1 * std::min(1., std::max(0., tiles - 2)) + 2.5 * std::max(0., tiles - 3);
+            const double up = two - one;
+            return rounds_ms(units, 2 * cu, room, {one, one, one, one + .77 * up, one + .88 * up, two});
+        }
         default: return rounds_ms(units, cu, room, {nw > 3 ? 31.0 : 28.9});
     }
 }
@@ -97,16 +101,21 @@ double joint_mont_ms(int bits, uint64_t jobs, uint64_t room, uint32_t cus) {
 
 // A number over a block (halves_group_kernel): blocks of 16 chunks modulo one
 // prime.  Its chain is 2 to 5 times shorter than the one-lane chain, but it takes
-// more of the chip per number.
+// more of the chip per number.  Up to a round (half a round) of resident blocks they end
+// together, beyond it a block goes on to its next as it ends.
 double group_ms(int bits, uint64_t blocks, uint32_t cus) {
-    const uint64_t cu = cus, all = ~0ull;
+    const uint64_t cu = cus;
+    auto ms = [&](uint64_t round, double half, double full) {
+        if (2 * blocks <= round) return half;
+        return blocks <= round ? full : (0.1 + (double)blocks / (double)round) * full;
+    };
     switch (bits) {
-        case 1024: return rounds_ms(blocks, 8 * cu, all, {0.85, 0.92, 1.4, 1.77});
-        case 2048: return rounds_ms(blocks, 4 * cu, all, {2.7, 3.05});
-        case 3072: return rounds_ms(blocks, 2 * cu, all, {3.65, 4.5});
-        case 4096: return rounds_ms(blocks, 2 * cu, all, {6.3, 8.1});
-        case 6144: return rounds_ms(blocks, cu, all, {15.2});
-        default: return rounds_ms(blocks, cu, all, {34.6, 48.7});
+        case 1024: return 2 * blocks > 8 * cu ? ms(8 * cu, 0.92, 1.77) : ms(4 * cu, 0.85, 0.92);
+        case 2048: return ms(4 * cu, 2.7, 3.05);
+        case 3072: return ms(2 * cu, 3.65, 4.5);
+        case 4096: return ms(2 * cu, 6.3, 8.0);
+        case 6144: return ms(cu, 15.2, 15.2);
+        default: return ms(cu, 34.6, 48.7);
     }
 }
 
@@ -125,17 +134,18 @@ static bool group_fits(const ClassRun &r) {
 
 bool group_rest(const ClassRun &r, uint32_t groups, uint32_t cus) {
     return fold_lane_block(kClassBits[r.cls]) > 2 && r.tail_lanes > 0 && r.fill_lanes > 1 && group_fits(r) &&
-           group_rest_ms(r, groups, cus) < lane_ms(kClassBits[r.cls], r.group_tiles, 2ull * groups, ~0ull, cus);
+           group_rest_ms(r, groups, cus) < lane_ms(kClassBits[r.cls], r.group_tiles, (double)r.ntiles / r.ngroups, 2ull * groups, ~0ull, cus);
 }
 
 // The lane form of a launch, its partial round spread over blocks where that is faster.
 static double lane_launch_ms(const ClassRun &r, uint64_t room, uint32_t cus) {
     const int bits = kClassBits[r.cls];
     const uint32_t round = std::max(1u, bits > 3072 ? cus / 2 : cus), rest = r.ngroups % round;  // groups (3072, 4096 bits)
+    const double tiles = (double)r.ntiles / r.ngroups;
     room /= r.group_tiles;
     if (r.group_tiles > 1 && rest && r.ngroups > round && room >= 2 * round && group_rest(r, rest, cus))
-        return lane_ms(bits, r.group_tiles, 2ull * (r.ngroups - rest), room, cus) + group_rest_ms(r, rest, cus);
-    return lane_ms(bits, r.group_tiles, 2ull * r.ngroups, room, cus);
+        return lane_ms(bits, r.group_tiles, tiles, 2ull * (r.ngroups - rest), room, cus) + group_rest_ms(r, rest, cus);
+    return lane_ms(bits, r.group_tiles, tiles, 2ull * r.ngroups, room, cus);
 }
 
 bool mont_launch(const ClassRun &r, uint32_t cus) {
@@ -165,7 +175,7 @@ bool fills_chip(const ClassRun &r_, uint32_t classes, uint32_t cus) {
     if (!fold_group(bits).nl || group_launch(r, cus)) return false;
     r.share = 1;
     const uint64_t waves = group_launch(r, cus) ? 2ull * r.parts * fold_group_block(bits) : 2ull * r.ntiles;
-    return waves >= 2 * (uint64_t)cus;
+    return waves >= cus;
 }
 
 bool joint_mont_launch(const ClassRun &r, uint32_t cus) {

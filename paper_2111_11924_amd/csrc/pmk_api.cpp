@@ -626,6 +626,7 @@ int batch_sequence(pmk_plan *pl, int decrypt, const uint8_t *in, uint8_t *out, v
             // partial round stays in its launch, where its waves start as soon as
             // waves of that launch finish
             r.share = (uint32_t)nl;
+            r.busy = true;
             if (!fold_group(kClassBits[order[i]]).nl) r.fill_lanes = 1;
             r.tail_lanes = 0;
         } else if (decrypt && lanes > 1) {

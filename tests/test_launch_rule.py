@@ -85,7 +85,9 @@ def shape(blinded, bits, keys, chunks, cap=0):
 # groups of mixed sizes, the last ones spread over blocks (L): job tiles, parts, groups of
 # the shape, ms
 MIXED = [(4096, 722, 1240, 140, 4, dict(L=35.5, M=42.7)), (4096, 1044, 1900, 174, 4, dict(L=49.0, M=84.1)),
-         (3072, 722, 1240, 140, 4, dict(L=23.9, M=17.9)), (3072, 1044, 1900, 174, 4, dict(L=25.5, M=37.0))]
+         (3072, 722, 1240, 140, 4, dict(L=23.9, M=17.9)), (3072, 1044, 1900, 174, 4, dict(L=25.5, M=37.0)),
+         (4096, 506, 810, 129, 4, dict(G=31.4, M=42.6)), (3072, 544, 855, 129, 4, dict(G=19.2, L=23.0, M=17.8)),
+         (3072, 436, 697, 128, 4, dict(G=15.6, L=14.9, M=18.0))]
 
 
 @pytest.fixture(scope="module")
