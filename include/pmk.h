@@ -243,12 +243,13 @@ int pmk_get_window(const pmk_ctx *ctx, uint32_t bits);
  *     own with `tail_lanes` lanes per number, or the largest smaller power of two
  *     whose waves fit one round.
  *   - 1024- to 4096-bit keys run one lane per number with the reduction on the
- *     matrix cores; with `fill_lanes` above 1 a launch of few numbers spreads each
+ *     matrix cores, or with Montgomery products where the keys have too few chunks
+ *     each; with `fill_lanes` above 1 a launch of few numbers spreads each
  *     over a block of up to 4 waves instead (blinded decryption: 8 or 4 lanes at
- *     2048 to 4096 bits), and so does a partial round where a SIMD holds one wave.
- *   - 6144- and 8192-bit keys run 4 lanes per number with `fill_lanes` 4, and
- *     each number over a block of 7 or 8 waves with 8 (blinded decryption: 8
- *     lanes in a small launch); their `tail_lanes` must be 4.
+ *     2048 to 4096 bits, 2 at 4096), and so does a partial round at 3072 and 4096.
+ *   - 6144- and 8192-bit keys run 4 lanes per number with `fill_lanes` 4; with 8
+ *     each number over a block of 7 or 8 waves where that is faster (blinded
+ *     decryption: 8 lanes in a small launch); their `tail_lanes` must be 4.
  * The one-lane classes take 1, 2 or 4, and `fill_lanes` 8 at 2048, 3072 and 4096
  * bits (PMK_EUNSUPPORTED for other supported counts, PMK_EINVAL for counts other
  * than 1, 2, 4, 8).  Results never change; graphs are recaptured; PMK_EBUSY while
@@ -465,8 +466,8 @@ int pmk_miller_rabin(pmk_ctx *ctx, uint32_t bits, const uint32_t *d_cand, uint32
  * pmk_server_start: staging_bytes (0: 512 MiB) is the admission budget of
  *   device memory for inputs and outputs in flight (with a pinned host mirror
  *   of the same size, through which the copies run asynchronously beside the
- *   rounds); round_chunks (0: two
- *   chip-filling rounds of 2048-bit CRT halves) bounds the chunks of one
+ *   rounds); round_chunks (0: two chip-filling rounds of 2048-bit CRT halves with
+ *   three waves per SIMD, 196,608 on 256 compute units) bounds the chunks of one
  *   round; pipeline_depth as in the struct.  The key table and window widths may not change while the server
  *   runs (PMK_EBUSY).  PMK_EBUSY if a server already runs.
  * pmk_submit (thread-safe): validates like pmk_plan_create (PMK_EKEY,

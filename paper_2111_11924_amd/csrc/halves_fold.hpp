@@ -347,7 +347,7 @@ int lone_rounds(uint32_t units, uint32_t grid, uint32_t cus, Launch launch) {
 
 // The partial round after full ones, as blocks of two units (group, h): four waves,
 // one on each SIMD, which blocks of one or two waves do not ensure after the full
-// rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 4.5
+// rounds (1,024 2048-bit jobs: 7.2 ms in blocks of one wave, some SIMDs two deep, 4.6
 // ms here; 15 MB under 1024-bit keys 4.46 / 3.90 ms; from an idle chip blocks of one
 // wave are as even and 3 to 7 % faster).  table and entry hold two tables and four rows,
 // and fill LDS so that one block fewer fits a compute unit than the class has waves per SIMD.

@@ -24,8 +24,8 @@
 //
 // Bound by the chain of one number: per product the columns, the MFMA steps and the
 // four exchanges follow one another.  1 MiB under 64 2048-bit keys 4.38 ms with
-// four lanes per number, 2.98 here; 100 KiB under 16 keys 17.1 / 6.3 ms at 4096
-// bits, 43.6 / 16.2 at 6144 and 94.3 / 39.3 at 8192 with eight.
+// four lanes per number, 2.95 here; 100 KiB under 16 keys 17.1 / 6.3 ms at 4096
+// bits, 43.6 / 15.8 at 6144 and 94.3 / 34.5 at 8192 with eight.
 #pragma once
 
 namespace pmk {

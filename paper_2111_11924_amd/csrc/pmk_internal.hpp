@@ -446,7 +446,7 @@ uint32_t table_units(const ClassRun &r);
 // table words per block, blocks that are resident, and the launch, which leaves
 // fold results in r.half; launch_halves_group takes the tiles from that of group
 // `first` on (r.groups; 0: all of them)
-PMK_HD constexpr uint32_t group_units(uint32_t tiles) { return (tiles + 3) / 4 * 32; }
+PMK_HD constexpr uint32_t group_units(uint32_t tiles) { return (tiles + 3) / 4 * 32; }  // parts of jobs, in eights
 uint64_t group_slot_words(int cls, int win);
 uint32_t group_resident(int cls);
 int launch_halves_group(const ClassRun &r, uint32_t first, void *stream);
