@@ -216,15 +216,29 @@ int pmk_keys_load(pmk_ctx *ctx, const pmk_key *keys, uint32_t nkeys) {
     }
     // fold tables, where they fit: 15 to 57 times the records' size
     for (int c = 0; c < kNumClasses && e == hipSuccess; ++c) {
-        const uint64_t fb = counts[c] ? fold_bytes_per_key(c) * counts[c] : 0;
+        const uint64_t fb = counts[c] ? fold_bytes_per_key(c) * counts[c] : 0, words = fb ? fold_setup_words(c, counts[c]) : 0;
         if (!fb) continue;
-        if (hipMalloc(&fold[c], fb) != hipSuccess) {
-            (void)hipGetLastError();  // a class without them decrypts by Montgomery products
+        uint64_t *sums = nullptr;
+        auto make = [&] {
+            if (hipMalloc(&fold[c], fb) == hipSuccess && hipMalloc(&sums, words * sizeof(uint64_t)) == hipSuccess) return true;
+            if (fold[c]) (void)hipFree(fold[c]);
             fold[c] = nullptr;
-            continue;
+            (void)hipGetLastError();
+            return false;
+        };
+        if (!make()) {
+            // the previous table's make room (no plan uses it; its keys, should this load
+            // fail, decrypt by Montgomery products, as a class without fold tables does)
+            for (auto &p : ctx->d_fold) {
+                if (p) (void)hipFree(p);
+                p = nullptr;
+            }
+            if (!make()) continue;
         }
         e = hipMemset(fold[c], 0, fb);
-        if (e == hipSuccess) e = (hipError_t)launch_fold_setup(c, fresh[c], counts[c], fold[c], nullptr);
+        if (e == hipSuccess) e = (hipError_t)launch_fold_setup(c, fresh[c], counts[c], fold[c], sums, words, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        (void)hipFree(sums);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {

@@ -317,8 +317,11 @@ int launch_pack(const ClassRun &r, const uint8_t *src, int decrypt, void *stream
 int launch_encrypt(const ClassRun &r, void *stream);
 int launch_decrypt_halves(const ClassRun &r, void *stream);
 int launch_garner(const ClassRun &r, void *stream);
-// fold tables of a class's `count` key records (kfold.hip), two per key
-int launch_fold_setup(int cls, const uint32_t *keys, uint32_t count, uint8_t *fold, void *stream);
+// fold tables of a class's `count` key records (kfold.hip), two per key; `sums`: a buffer of
+// `words` = fold_setup_words words for as long as that runs
+uint64_t fold_setup_words(int cls, uint32_t count);
+int launch_fold_setup(int cls, const uint32_t *keys, uint32_t count, uint8_t *fold, uint64_t *sums, uint64_t words,
+                      void *stream);
 inline uint64_t fold_bytes_per_key(int cls) { return 2ull * fold_table(kClassBits[cls]).size; }
 // Groups of up to `per` tiles under one key (ClassRun::groups) of a class's
 // tiles, appended to out: each key's tiles in the fewest groups, of equal sizes up to one.

@@ -53,3 +53,38 @@ def test_tables_that_do_not_fit(bits, count):
         del hog
         torch.cuda.empty_cache()
         ctx.close()
+
+
+def test_reload_frees_the_previous_tables():
+    """A table whose fold tables fit only once: loading it again keeps them."""
+    import torch
+
+    pairs = cases._pairs(2048)
+    keys = [cases._key(2048, *pairs[i % len(pairs)]) for i in range(6600)]  # 0.65 GiB of fold tables
+    ctx = binding.Context(0)
+    ctx.load_keys(keys[:1])
+    torch.cuda.synchronize()
+    hog = [torch.empty(torch.cuda.mem_get_info()[0] - (1280 << 20), dtype=torch.uint8, device="cuda")]
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            while len(hog) < 64:
+                hog.append(torch.empty(256 << 20, dtype=torch.uint8, device="cuda"))
+        del hog[-5:]
+        torch.cuda.empty_cache()
+        for _ in range(2):
+            ctx.load_keys(keys)
+            with pytest.raises(torch.cuda.OutOfMemoryError):  # the tables are there
+                hog.append(torch.empty(768 << 20, dtype=torch.uint8, device="cuda"))
+        del hog[-2:]
+        torch.cuda.empty_cache()
+        km = np.repeat(np.array([0, 6599], np.uint32), [30, 40])
+        msg = inputs.make_message(len(km) * 252, 6)
+        plan = ctx.plan(km, len(msg))
+        out = plan.decrypt(plan.encrypt(torch.from_numpy(msg).cuda()))
+        assert plan.check() == binding.PMK_OK
+        np.testing.assert_array_equal(out[: len(msg)].cpu().numpy(), msg)
+        plan.close()
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+        ctx.close()
