@@ -183,3 +183,12 @@ def test_edges_under_different_keys(ctx, bits, lanes):
         plan.close()
     finally:
         ctx.set_lanes(bits, *old)
+
+
+# the last step of the group form has fewer jobs: tiles with up to two parts, each in its
+# quarter of the blocks, and tiles with most of their four
+@pytest.mark.parametrize("bits,keys,chunks", [
+    (1024, 270, 25), (2048, 228, 25), (2048, 131, 16), (2048, 90, 90), (3072, 100, 25), (3072, 66, 16), (3072, 18, 300),
+    (4096, 100, 25), (4096, 65, 64), (6144, 50, 25), (8192, 33, 17)])
+def test_last_step_of_group_blocks(ctx, bits, keys, chunks):
+    check(ctx, bits, keys, chunks, False)
