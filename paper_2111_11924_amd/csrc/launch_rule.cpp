@@ -101,22 +101,34 @@ double joint_mont_ms(int bits, uint64_t jobs, uint64_t room, uint32_t cus) {
 
 // A number over a block (halves_group_kernel): blocks of 16 chunks modulo one
 // prime.  Its chain is 2 to 5 times shorter than the one-lane chain, but it takes
-// more of the chip per number.  Up to a round (half a round) of resident blocks they end
-// together, beyond it a block goes on to its next as it ends.
+// more of the chip per number.  Up to half a round of resident blocks takes `half`, a
+// round `full`; after full rounds the blocks that go on are those that ended first, so that
+// a rest of up to one block per compute unit takes `few` or less, a larger one `rest`.
 double group_ms(int bits, uint64_t blocks, uint32_t cus) {
     const uint64_t cu = cus;
-    auto ms = [&](uint64_t round, double half, double full) {
-        if (2 * blocks <= round) return half;
-        return blocks <= round ? full : (0.1 + (double)blocks / (double)round) * full;
+    auto ms = [&](uint64_t round, double half, double full, double few, double rest) {
+        if (blocks <= round) return 2 * blocks <= round ? half : full;
+        const uint64_t left = blocks % round;
+        const double part = left ? std::min(1., 0.3 + 2. * (double)left / (double)cu) : 0.;
+        return (double)(blocks / round) * full + (left > cu ? rest : part * few);
     };
     switch (bits) {
-        case 1024: return 2 * blocks > 8 * cu ? ms(8 * cu, 0.92, 1.77) : ms(4 * cu, 0.85, 0.92);
-        case 2048: return ms(4 * cu, 2.7, 3.05);
-        case 3072: return ms(2 * cu, 3.65, 4.5);
-        case 4096: return ms(2 * cu, 6.3, 8.0);
-        case 6144: return ms(cu, 15.2, 15.2);
-        default: return ms(cu, 34.6, 48.7);
+        case 1024: return rounds_ms(blocks, 8 * cu, ~0ull, {0.85, 0.92, 1.14, 1.77});
+        case 2048: return ms(4 * cu, 2.7, 3.05, 1.55, 2.6);
+        case 3072: return ms(2 * cu, 3.65, 4.5, 3.05, 4.5);
+        case 4096: return ms(2 * cu, 6.3, 8.1, 5.1, 8.1);
+        case 6144: return ms(cu, 15.4, 15.4, 15.4, 15.4);
+        default: return ms(cu, 34.6, 47.0, 47.0, 47.0);
     }
+}
+
+// Classes side by side share the chip, each as if all had its blocks: a step of one's blocks runs
+// beside the others', there are no rounds (four classes with 36 keys and 71 chunks: 17.4 ms,
+// 29.6 where the 4096-bit class counts whole rounds and takes the lane form).
+double beside_ms(int bits, uint64_t blocks, uint32_t cus) {
+    const double full = (double)cus * (bits < 2048 ? 8 : (bits < 3072 ? 4 : (bits < 6144 ? 2 : 1)));
+    const double round = group_ms(bits, (uint64_t)full, cus), x = (double)blocks / full;
+    return x <= 1 ? group_ms(bits, blocks, cus) : (0.1 + x) * round;
 }
 
 }  // namespace
@@ -162,10 +174,10 @@ bool group_launch(const ClassRun &r, uint32_t cus) {
     const uint64_t room = room_of(r, table_words_per_slot(r.cls, 1, r.win));
     double other = mont_ms(bits, 2ull * r.ntiles, room, r.busy, cus);
     if (fold_lane(bits).nl) other = std::min(other, lane_launch_ms(r, room, cus));
-    // where most tiles have most of their parts, some block finds one at each of its steps
-    const uint64_t blocks = r.parts > 2 * r.ntiles ? 8ull * r.ntiles : 2ull * r.parts;
-    // classes side by side share the chip
-    return group_ms(bits, blocks * std::max(1u, r.share), cus) < other;
+    const double ms = r.share > 1 ? beside_ms(bits, 2ull * r.parts * r.share, cus)
+                      // where tiles have about three of their four parts, some block finds one at each of its steps
+                      : group_ms(bits, r.parts > 2 * r.ntiles && 4 * r.parts <= 13 * r.ntiles ? 8ull * r.ntiles : 2ull * r.parts, cus);
+    return ms < other;
 }
 
 bool fills_chip(const ClassRun &r_, uint32_t classes, uint32_t cus) {
