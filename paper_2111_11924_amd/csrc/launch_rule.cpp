@@ -118,7 +118,7 @@ double group_ms(int bits, uint64_t blocks, uint32_t cus) {
         case 3072: return ms(2 * cu, 3.65, 4.5, 3.05, 4.5);
         case 4096: return ms(2 * cu, 6.3, 8.1, 5.1, 8.1);
         case 6144: return ms(cu, 15.4, 15.4, 15.4, 15.4);
-        default: return ms(cu, 34.6, 47.0, 47.0, 47.0);
+        default: return ms(cu, 34.2, 34.2, 34.2, 34.2);
     }
 }
 

@@ -29,8 +29,8 @@ PLAIN = [
     (4096, 1024, 64, dict(L=226.6, M=86.4)), (4096, 256, 256, dict(L=62.0, M=86.4)),
     (6144, 64, 64, dict(G=30.5, M=68.0)), (6144, 128, 64, dict(G=59.6, M=66.3)),
     (6144, 256, 64, dict(G=117.4, M=111.5)), (6144, 512, 64, dict(G=235.1, M=221.7)),
-    (8192, 64, 64, dict(G=94.1, M=146.2)), (8192, 128, 64, dict(G=185.4, M=154.2)),
-    (8192, 256, 64, dict(G=367.7, M=260.1)), (8192, 512, 64, dict(G=735.2, M=515.4)),
+    (8192, 64, 64, dict(G=67.4, M=146.2)), (8192, 128, 64, dict(G=132.3, M=154.2)),
+    (8192, 256, 64, dict(G=262.0, M=260.1)), (8192, 512, 64, dict(G=524.6, M=515.4)),
 ]
 BLINDED = [
     (1024, 512, 192, dict(L=4.72, M=4.27)), (1024, 1024, 64, dict(L=2.48, M=2.84)),
