@@ -70,7 +70,7 @@ PEAK_MAD_PER_S = 256 * 64 * 2.4e9
 # copy (bench.py --copy-probe 256: FETCH_SIZE reads half the bytes moved,
 # WRITE_SIZE all of them).  Valid only for the kernel sources it was measured
 # on (hash below); reported as null otherwise.
-HALVES_TRAFFIC = {"sources_sha256": "48e439955819dcb16e392531a328c7db41cd5387cd55430268ea99407e1c8e17",
+HALVES_TRAFFIC = {"sources_sha256": "3dc655d6f4d67cc971d683b15f3b58950120fea8928d07ab2c218c6db418b1f9",
                   "fetch_bytes": 18_461_554_176, "write_bytes": 2_745_294_720}
 KERNEL_SOURCES = ["paper_2111_11924_amd/csrc/kernels_impl.hpp", "paper_2111_11924_amd/csrc/mont.hpp",
                   "paper_2111_11924_amd/csrc/mont_lanes.hpp", "paper_2111_11924_amd/csrc/pmk_internal.hpp",
